@@ -13,12 +13,14 @@
 //          order inside a column is arbitrary here)
 //   sort   every column in ascending row order, which makes the result
 //          unique: columns of up to kShort entries by one lane with a
-//          sorting network, longer ones by a wavefront that counts rows in
-//          LDS and writes them out in order
+//          sorting network, longer ones by a wavefront, the longest by the
+//          workgroup
 // Every index a phase derives
 // from device data is range-checked; a violation flags samp::kErrRange in
 // counts[3] and skips the access.
 #pragma once
+
+#include <type_traits>
 
 #include "internal.h"
 #include "sampler_dev.h"
@@ -30,9 +32,6 @@ constexpr int kThreads = 256;
 constexpr int kPer = 8;                          // columns per thread in the scan
 constexpr int64_t kScanTile = kThreads * kPer;   // columns per scan workgroup
 constexpr int kShort = 16;                       // longest column sorted by one lane
-// rows counted per LDS pass of a long column; its 8 KB of LDS per workgroup
-// is reserved by every launch the sort rides in, so it stays small
-constexpr int kWindow = 1024;
 
 struct Args {
     int64_t *counts;         // block counts: n_dst, n_src, nnz, error flag
@@ -45,6 +44,7 @@ struct Args {
     int64_t nb_scan;
     int64_t *cscptr;         // [cap_src + 1]
     int32_t *cscrow;         // [cap_nnz]
+    int64_t cap_dst;         // most rows of the block
 };
 
 struct ScanJob {
@@ -143,102 +143,243 @@ __device__ __forceinline__ void wave_sync_lds() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// One wavefront: the rows of column segment out[0, len) in ascending order.
-// Rows are counted into 16-bit LDS counters (two per word), kWindow rows at
-// a time, and written out in row order.  src is where the unsorted rows
-// are read (out itself when one window covers all rows, else a copy).
-__device__ __forceinline__ void sort_long(uint32_t *lds, const int32_t *src, int32_t *out, int64_t len,
-                                          int64_t n_dst, int64_t *err) {
+// One wavefront: sort seg[0, len) for kShort < len <= 64, one entry per lane
+// (v: the entry of this lane).  A lane's place is the number of smaller
+// entries, equal ones in lane order; len uniform steps of a readlane, a
+// compare and an add, with no exchange between lanes to wait for.
+__device__ __forceinline__ void sort_wave(int32_t *seg, int32_t v, int len) {
     const int lane = threadIdx.x & 63;
-    int64_t pos = 0;
-    for (int64_t w0 = 0; w0 < n_dst; w0 += kWindow) {
-        for (int64_t i = lane; i < len; i += 64) {
-            const int64_t r = src[i];
+    int rank = 0;
+    for (int s = 0; s < len; ++s) {
+        const int32_t o = __builtin_amdgcn_readlane(v, s);
+        rank += (s < lane ? o <= v : o < v) ? 1 : 0;
+    }
+    if (lane < len) seg[rank] = v;
+}
+
+// Exclusive scan of v over T = 64 (a wavefront) or kThreads threads.
+template <int T> __device__ __forceinline__ int excl_scan(int v) {
+    if constexpr (T == 64) {
+        const int lane = threadIdx.x & 63;
+        int inc = v;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += y;
+        }
+        return inc - v;
+    } else {
+        int64_t total;
+        return static_cast<int>(samp::block_excl_scan(v, &total));
+    }
+}
+
+// T threads: sort seg[0, n), n <= half, through 2 * half LDS words.  Rows are
+// dealt to `half` buckets of equal row ranges; an entry's place is its
+// bucket's start plus the smaller entries of its bucket (equal ones in slot
+// order).  A hub's rows are spread over the block, so a bucket holds an
+// entry or two; a column whose rows crowd into one range costs up to n steps
+// per entry and stays correct.
+// P: most entries and buckets per thread (n and half at most P T).
+template <int T, int P, class Sync>
+__device__ __forceinline__ void sort_buckets(uint32_t *words, int half, int32_t *seg, int n, int n_dst, int t,
+                                             int64_t *err, Sync &&sync) {
+    uint32_t *start = words;
+    int32_t *key = reinterpret_cast<int32_t *>(words + half);
+    const bool direct = n_dst <= half;  // a bucket per row
+    const uint32_t scale =
+        direct ? 0u : static_cast<uint32_t>((static_cast<uint64_t>(half) << 32) / static_cast<uint32_t>(n_dst));
+    for (int i = t; i < half; i += T) start[i] = 0u;
+    int32_t v[P];
+    uint32_t b[P], at[P];
+#pragma unroll
+    for (int e = 0; e < P; ++e) v[e] = t + e * T < n ? seg[t + e * T] : 0;
+    sync();
+#pragma unroll
+    for (int e = 0; e < P; ++e) {
+        if (t + e * T >= n) continue;
+        const bool ok = v[e] >= 0 && v[e] < n_dst;
+        if (!ok) samp::flag_error(err, samp::kErrRange);
+        b[e] = !ok ? 0u : direct ? static_cast<uint32_t>(v[e]) : __umulhi(static_cast<uint32_t>(v[e]), scale);
+        at[e] = atomicAdd(&start[b[e]], 1u);
+    }
+    sync();
+    // counts -> starts; thread t owns buckets [per t, per (t + 1))
+    const int per = half / T;
+    uint32_t c[P];
+    int sum = 0;
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+        c[q] = q < per ? start[t * per + q] : 0u;
+        sum += static_cast<int>(c[q]);
+    }
+    uint32_t run = static_cast<uint32_t>(excl_scan<T>(sum));
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+        if (q < per) start[t * per + q] = run;
+        run += c[q];
+    }
+    sync();
+#pragma unroll
+    for (int e = 0; e < P; ++e)
+        if (t + e * T < n) key[start[b[e]] + at[e]] = v[e];
+    sync();
+#pragma unroll
+    for (int e = 0; e < P; ++e) {
+        if (t + e * T >= n) continue;
+        const uint32_t lo = start[b[e]], hi = b[e] + 1 < static_cast<uint32_t>(half) ? start[b[e] + 1] : n;
+        const uint32_t own = lo + at[e];
+        uint32_t place = lo;
+        for (uint32_t q = lo; q < hi; ++q) place += (key[q] < v[e] || (key[q] == v[e] && q < own)) ? 1u : 0u;
+        seg[place] = v[e];
+    }
+    sync();  // the next segment goes to the same words
+}
+
+// A workgroup: the rows of column segment out[0, len) in ascending order by
+// counting, 2 * words rows at a time, into 16-bit LDS counters (two per
+// word).  The counters are all zero before and after.  Thread t owns `per`
+// consecutive words' worth of rows; its word q is at q * kThreads + t, so that
+// the walk over the counters is free of bank conflicts.  src is where the
+// unsorted rows are read (out itself when one window covers all rows, else a
+// copy).
+__device__ __forceinline__ void sort_counting(uint32_t *lds, int words, const int32_t *src, int32_t *out, int len,
+                                              int n_dst, int64_t *err) {
+    const int t = threadIdx.x, per = words / kThreads, window = 2 * words;
+    int pos = 0;
+    for (int w0 = 0; w0 < n_dst; w0 += window) {
+        for (int i = t; i < len; i += kThreads) {
+            const int r = src[i];
             if (r < 0 || r >= n_dst) {
                 samp::flag_error(err, samp::kErrRange);
                 continue;
             }
-            if (r >= w0 && r < w0 + kWindow) {
-                const int64_t o = r - w0;
-                atomicAdd(&lds[o >> 1], 1u << (16 * (o & 1)));
-            }
+            const int o = r - w0, w = o >> 1;
+            if (o >= 0 && o < window) atomicAdd(&lds[(w % per) * kThreads + w / per], 1u << (16 * (o & 1)));
         }
-        wave_sync_lds();
-        const int64_t w1 = min(n_dst, w0 + kWindow);
-        for (int64_t rb = w0; rb < w1; rb += 64) {
-            const int64_t r = rb + lane;
-            uint32_t c = 0;
-            if (r < w1) {
-                const int64_t o = r - w0;
-                c = (lds[o >> 1] >> (16 * (o & 1))) & 0xffffu;
-            }
-            // exclusive scan of c over the wavefront
-            uint32_t inc = c;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const uint32_t y = __shfl_up(inc, d, 64);
-                if (lane >= d) inc += y;
-            }
-            const uint32_t tot = __shfl(inc, 63, 64);
-            const int64_t at = pos + inc - c;
-            for (uint32_t q = 0; q < c; ++q)
-                if (at + q < len) out[at + q] = static_cast<int32_t>(r);
-            pos += tot;
+        __syncthreads();
+        int mine = 0;
+        for (int q = 0; q < per; ++q) {
+            const uint32_t c = lds[q * kThreads + t];
+            mine += static_cast<int>((c & 0xffffu) + (c >> 16));
         }
-        wave_sync_lds();
-        // clear the window's counters
-        for (int64_t o = lane; o < kWindow / 2; o += 64) lds[o] = 0u;
-        wave_sync_lds();
+        int64_t total;
+        int at = pos + static_cast<int>(samp::block_excl_scan(mine, &total));
+        for (int q = 0; mine > 0 && q < per; ++q) {
+            const uint32_t c = lds[q * kThreads + t];
+            const int r = w0 + 2 * (t * per + q);
+            for (uint32_t n = c & 0xffffu; n > 0; --n, ++at)
+                if (at < len) out[at] = r;
+            for (uint32_t n = c >> 16; n > 0; --n, ++at)
+                if (at < len) out[at] = r + 1;
+            lds[q * kThreads + t] = 0u;
+        }
+        pos += static_cast<int>(total);
+        __syncthreads();
+        if (w0 > n_dst - window) break;  // (w0 + window may not fit an int)
     }
 }
 
-struct SortJob {
+// The sort phase.  A workgroup takes 256 columns at a time: a thread sorts
+// its column in registers when it is short; longer ones go to two lists, one
+// walked by the wavefronts (a column per wavefront) and one by the whole
+// workgroup.  It is bound by latency (each list entry is a chain of one load,
+// a few LDS passes and one store), so what counts is that few columns follow
+// one another in one wavefront and that none walks all rows alone.
+// Long columns come from the graph's hubs: a wavefront that counted the rows
+// of every column above 16 entries by itself, 1,024 rows per pass, took 223 us
+// for the second block of 1,024 targets (7.6k rows, 69k edges, fanouts 25 and
+// 10) and 5.5 ms for that of 16,384 targets (83k rows, 719k edges); this form
+// takes 10 and 26 us.
+//
+// P sets the LDS words (512 P) and the entries a thread holds.  2 when the
+// block's rows fit one counting window of those words (2,048), else 8: the
+// larger area keeps the number of windows down for hubs of large blocks, but
+// its registers cost occupancy in the launches that the sort rides in (99
+// VGPRs instead of 71 beside layer 1's aggregation: a pipelined step of 1,024
+// targets lost 2.5%).
+template <int P> struct SortJob {
     Args a;
     __device__ void run(int64_t blk, int64_t nblk) const {
-        __shared__ uint32_t lds[kThreads / 64][kWindow / 2];
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        const int64_t n_dst = a.counts[0];
+        constexpr int words = 512 * P, wave_words = words / (kThreads / 64);
+        __shared__ __attribute__((aligned(16))) uint32_t sort_lds[words];
+        // wavefront columns from the front, workgroup columns from the back
+        __shared__ uint2 list[kThreads];  // segment (from the first column's), length
+        __shared__ int wave_n, group_n;
+        const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+        const int n_dst = static_cast<int>(min(a.counts[0], a.cap_dst));  // (local ids are 32-bit)
         const int64_t n_src = min(a.counts[1], a.cap_src);
         const int64_t nnz = min(a.counts[2], a.cap_nnz);
-        uint32_t *mine = lds[wave];
-        for (int64_t o = lane; o < kWindow / 2; o += 64) mine[o] = 0u;
-        wave_sync_lds();
-        const int64_t waves = nblk * (kThreads / 64);
-        for (int64_t g = blk * (kThreads / 64) + wave; g * 64 < n_src; g += waves) {
-            const int64_t c = g * 64 + lane;
+        // every thread of the workgroup runs the same rounds
+        for (int64_t c0 = blk * kThreads; c0 < n_src; c0 += nblk * kThreads) {
+            if (t == 0) wave_n = group_n = 0;
+            __syncthreads();
+            const int64_t c = c0 + t;
+            const int64_t base = a.cscptr[c0];
             int64_t p0 = 0, len = 0;
             if (c < n_src) {
                 p0 = a.cscptr[c];
                 const int64_t p1 = a.cscptr[c + 1];
-                if (p0 < 0 || p1 < p0 || p1 > nnz) {
+                if (base < 0 || p0 < base || p1 < p0 || p1 > nnz || p0 - base > UINT32_MAX || p1 - p0 > INT32_MAX)
                     samp::flag_error(&a.counts[3], samp::kErrRange);
-                    p0 = 0;
-                } else {
+                else
                     len = p1 - p0;
-                }
             }
-            if (len >= 2 && len <= kShort) sort_short(a.cscrow + p0, len);
-            uint64_t longs = __ballot(len > kShort);
-            while (longs) {
-                const int l = __builtin_ctzll(longs);
-                longs &= longs - 1;
-                const int64_t q0 = __shfl(p0, l, 64);
-                const int64_t ql = __shfl(len, l, 64);
-                int32_t *out = a.cscrow + q0;
+            if (len > kShort) {
+                const bool by_wave = len <= wave_words / 2;
+                const int at = by_wave ? atomicAdd(&wave_n, 1) : kThreads - 1 - atomicAdd(&group_n, 1);
+                list[at] = make_uint2(static_cast<uint32_t>(p0 - base), static_cast<uint32_t>(len));
+            } else if (len >= 2) {
+                sort_short(a.cscrow + p0, len);
+            }
+            __syncthreads();
+            const int nw = wave_n, ng = group_n;
+            for (int i = wave; i < nw; i += kThreads / 64) {
+                int32_t *seg = a.cscrow + base + list[i].x;
+                const int n = __builtin_amdgcn_readfirstlane(static_cast<int>(list[i].y));
+                if (n <= 64)
+                    sort_wave(seg, lane < n ? seg[lane] : 0, n);
+                else
+                    sort_buckets<64, P>(sort_lds + wave * wave_words, wave_words / 2, seg, n, n_dst, lane, &a.counts[3],
+                                     [] { wave_sync_lds(); });
+            }
+            __syncthreads();  // the LDS words change hands
+            bool zeroed = false;
+            for (int i = 0; i < ng; ++i) {
+                const uint2 item = list[kThreads - 1 - i];
+                int32_t *out = a.cscrow + base + item.x;
+                const int n = static_cast<int>(item.y);
+                if constexpr (P > 2) {  // (at P = 2 one window holds all rows)
+                    if (n_dst > 2 * words && n <= words / 2) {
+                        sort_buckets<kThreads, P>(sort_lds, words / 2, out, n, n_dst, t, &a.counts[3],
+                                                  [] { __syncthreads(); });
+                        zeroed = false;
+                        continue;
+                    }
+                }
+                if (!zeroed)
+                    for (int o = t; o < words; o += kThreads) sort_lds[o] = 0u;
+                zeroed = true;
                 const int32_t *src = out;
-                if (n_dst > kWindow) {
+                if (n_dst > 2 * words) {
                     // several windows read the rows again: keep a copy in the
                     // edge-row scratch (free once the edges are placed)
-                    int32_t *copy = a.erow + q0;
-                    for (int64_t i = lane; i < ql; i += 64) copy[i] = out[i];
-                    wave_sync_lds();
+                    int32_t *copy = a.erow + base + item.x;
+                    for (int e = t; e < n; e += kThreads) copy[e] = out[e];
                     src = copy;
                 }
-                sort_long(mine, src, out, ql, n_dst, &a.counts[3]);
+                __syncthreads();
+                sort_counting(sort_lds, words, src, out, n, n_dst, &a.counts[3]);
             }
+            __syncthreads();  // the lists are free for the next round
         }
     }
 };
+// f(tag) with the P (an integral constant) of a block of cap_dst rows.
+template <class F> void with_sort_size(int64_t cap_dst, F &&f) {
+    if (cap_dst <= 2048) f(std::integral_constant<int, 2>{});
+    else f(std::integral_constant<int, 8>{});
+}
 
 struct Grids {
     unsigned scan, place, sort;

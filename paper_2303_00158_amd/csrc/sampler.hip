@@ -152,6 +152,7 @@ csc::Args csc_args(const gnn_block *out, void *csc_ws, int64_t ws_src, int64_t w
     a.nb_scan = ceil_div(a.cap_src + 1, csc::kScanTile);
     a.cscptr = out->cscptr;
     a.cscrow = out->cscrow;
+    a.cap_dst = out->cap_dst;
     return a;
 }
 
@@ -167,7 +168,11 @@ gnn_status launch_block_csc(const csc::Args &a, hipStream_t s) {
     const csc::Grids g = csc_grids(a);
     GNN_TRY(launch_job(csc::ScanJob{a}, g.scan, s, "csc_scan"));
     GNN_TRY(launch_job(csc::PlaceJob{a}, g.place, s, "csc_place"));
-    return launch_job(csc::SortJob{a}, g.sort, s, "csc_sort");
+    gnn_status st = GNN_OK;
+    csc::with_sort_size(a.cap_dst, [&](auto p) {
+        st = launch_job(csc::SortJob<decltype(p)::value>{a}, g.sort, s, "csc_sort");
+    });
+    return st;
 }
 
 size_t sampler_shared_bytes(int64_t graph_n) { return shared_layout(graph_n).total; }

@@ -161,7 +161,12 @@ gnn_status run_prepare(const gnn_model *m, const gnn_graph *g, const float *gcn_
     }
     auto place = [&](int h) { return role(csc::PlaceJob{ca[h >= 0 ? h : 0]}, h >= 0 ? cg[h].place : 0u); };
     auto scan = [&](int h) { return role(csc::ScanJob{ca[h >= 0 ? h : 0]}, h >= 0 ? cg[h].scan : 0u); };
-    auto sort = [&](int h) { return role(csc::SortJob{ca[h >= 0 ? h : 0]}, h >= 0 ? cg[h].sort : 0u); };
+    // f(role) with the sort role of block h
+    auto with_sort = [&](int h, auto &&f) {
+        csc::with_sort_size(o.cap_dst[h >= 0 ? h : 0], [&](auto p) {
+            f(role(csc::SortJob<decltype(p)::value>{ca[h >= 0 ? h : 0]}, h >= 0 ? cg[h].sort : 0u));
+        });
+    };
 
     // hop 1 around the targets, then outwards; hop h's relabel only needs
     // hop h's sources, like hop h+1's prepare
@@ -188,11 +193,13 @@ gnn_status run_prepare(const gnn_model *m, const gnn_graph *g, const float *gcn_
         });
         GNN_TRY(st);
         if (h >= 2)
-            GNN_TRY(launch_jobs(s, "hop_emit+csc_scan+csc_sort", role(samp::EmitJob{plan[h].a}, plan[h].emit_grid),
-                                scan(h - 1), sort(h - 2)));
+            with_sort(h - 2, [&](auto sort) {
+                st = launch_jobs(s, "hop_emit+csc_scan+csc_sort", role(samp::EmitJob{plan[h].a}, plan[h].emit_grid),
+                                 scan(h - 1), sort);
+            });
         else
-            GNN_TRY(launch_jobs(s, "hop_emit+csc_scan", role(samp::EmitJob{plan[h].a}, plan[h].emit_grid),
-                                scan(h - 1)));
+            st = launch_jobs(s, "hop_emit+csc_scan", role(samp::EmitJob{plan[h].a}, plan[h].emit_grid), scan(h - 1));
+        GNN_TRY(st);
     }
     // feature loading (rows of the input layer's sources) with the last
     // hop's relabel
@@ -216,13 +223,17 @@ gnn_status run_prepare(const gnn_model *m, const gnn_graph *g, const float *gcn_
                                 static_cast<const float *>(table), row_stride,
                                 reinterpret_cast<const uint16_t *>(prep + o.x0), m->dims[0],
                                 reinterpret_cast<uint16_t *>(prep + o.agg[1]), [&](auto aj) {
-            st = launch_jobs(s, "csc_sort+aggregate_l1_from_table", sort(L - 2), role(aj, agg::row_grid(b0.cap_dst)));
+            with_sort(L - 2, [&](auto sort) {
+                st = launch_jobs(s, "csc_sort+aggregate_l1_from_table", sort, role(aj, agg::row_grid(b0.cap_dst)));
+            });
         });
         return st;
     }
     // (layer 1's argmax is not kept: no aggregation backward below layer 2)
     agg::with_fwd_kind_job(&b0, m->kind, prep + o.x0, act, m->dims[0], prep + o.agg[1], act, nullptr, [&](auto aj) {
-        st = launch_jobs(s, "csc_sort+aggregate_l1", sort(L - 2), role(aj, agg::row_grid(b0.cap_dst)));
+        with_sort(L - 2, [&](auto sort) {
+            st = launch_jobs(s, "csc_sort+aggregate_l1", sort, role(aj, agg::row_grid(b0.cap_dst)));
+        });
     });
     return st;
 }
@@ -278,8 +289,11 @@ gnn_status run_prepare_group(const gnn_model *m, const gnn_graph *g, const float
     auto scan = [&](int h) {
         return multi_role([&](int c) { return csc::ScanJob{ca[c][h >= 0 ? h : 0]}; }, G, h >= 0 ? cg[h].scan : 0u);
     };
-    auto sort = [&](int h) {
-        return multi_role([&](int c) { return csc::SortJob{ca[c][h >= 0 ? h : 0]}; }, G, h >= 0 ? cg[h].sort : 0u);
+    auto with_sort = [&](int h, auto &&f) {
+        csc::with_sort_size(o.cap_dst[h >= 0 ? h : 0], [&](auto p) {
+            f(multi_role([&](int c) { return csc::SortJob<decltype(p)::value>{ca[c][h >= 0 ? h : 0]}; }, G,
+                         h >= 0 ? cg[h].sort : 0u));
+        });
     };
     auto relabel = [&](int h) {
         return multi_role([&](int c) { return samp::RelabelJob{plan[c][h].a}; }, G, plan[0][h].relabel_grid);
@@ -303,8 +317,13 @@ gnn_status run_prepare_group(const gnn_model *m, const gnn_graph *g, const float
                              place(h - 2));
         });
         GNN_TRY(st);
-        if (h >= 2) GNN_TRY(launch_jobs(s, "hop_emit+csc_scan+csc_sort", emit(h), scan(h - 1), sort(h - 2)));
-        else GNN_TRY(launch_jobs(s, "hop_emit+csc_scan", emit(h), scan(h - 1)));
+        if (h >= 2)
+            with_sort(h - 2, [&](auto sort) {
+                st = launch_jobs(s, "hop_emit+csc_scan+csc_sort", emit(h), scan(h - 1), sort);
+            });
+        else
+            st = launch_jobs(s, "hop_emit+csc_scan", emit(h), scan(h - 1));
+        GNN_TRY(st);
     }
     const bool fuse = fused_loading(m, g, host_table, tdt, act);
     gath::Args ga[kMaxCopies];
@@ -352,8 +371,11 @@ gnn_status run_prepare_group(const gnn_model *m, const gnn_graph *g, const float
                     else same = false;
                 });
             if (same)
-                st = launch_jobs(s, "csc_sort+aggregate_l1_from_table", sort(L - 2),
-                                 multi_role([&](int c) { return js[c]; }, G, agg::row_grid(blk[0][L - 1].cap_dst)));
+                with_sort(L - 2, [&](auto sort) {
+                    st = launch_jobs(s, "csc_sort+aggregate_l1_from_table", sort,
+                                     multi_role([&](int c) { return js[c]; }, G,
+                                                agg::row_grid(blk[0][L - 1].cap_dst)));
+                });
         });
         GNN_CHECK(same, GNN_EINVAL, "train_step: prepare workspaces differ in alignment");
         return st;
@@ -369,8 +391,10 @@ gnn_status run_prepare_group(const gnn_model *m, const gnn_graph *g, const float
                 else same = false;
             });
         if (same)
-            st = launch_jobs(s, "csc_sort+aggregate_l1", sort(L - 2),
-                             multi_role([&](int c) { return js[c]; }, G, agg::row_grid(blk[0][L - 1].cap_dst)));
+            with_sort(L - 2, [&](auto sort) {
+                st = launch_jobs(s, "csc_sort+aggregate_l1", sort,
+                                 multi_role([&](int c) { return js[c]; }, G, agg::row_grid(blk[0][L - 1].cap_dst)));
+            });
     });
     GNN_CHECK(same, GNN_EINVAL, "train_step: prepare workspaces differ in alignment");
     return st;
