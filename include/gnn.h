@@ -145,8 +145,8 @@ typedef struct gnn_block {
  *   cap_nnz = cap_dst * fanout, cap_src = min(cap_dst + cap_nnz, graph_n). */
 gnn_status gnn_block_bounds(int64_t graph_n, int64_t cap_dst, int32_t fanout, int64_t *cap_src, int64_t *cap_nnz);
 
-/* Workspace of gnn_build_block.  It holds a per-vertex map and two
- * per-vertex bitmaps; the bitmaps must be zeroed once with
+/* Workspace of gnn_build_block.  It holds a per-vertex map and two maps of
+ * per-vertex marks; the marks must be zeroed once with
  * gnn_sampler_workspace_init and every gnn_build_block call leaves them zero
  * again.  One workspace serves any number of sequential calls on one
  * stream (calls that share it must not overlap). */

@@ -49,11 +49,13 @@ struct Args {
 
 struct ScanJob {
     Args a;
-    __device__ void run(int64_t, int64_t) const {
-        const int64_t t = samp::take_ticket(a.ticket);
+    __device__ void run(int64_t blk, int64_t) const {
         const int64_t n_src = min(a.counts[1], a.cap_src);
+        // workgroups that the capacity-sized grid has too many leave without
+        // a ticket (tickets are atomics on one address, 11.5 ns apart)
+        if (blk * kScanTile > n_src) return;
+        const int64_t t = samp::take_ticket(a.ticket);
         const int64_t j0 = t * kScanTile;
-        if (j0 > n_src) return;  // every later ticket is past the end as well
         const int64_t jt = j0 + static_cast<int64_t>(threadIdx.x) * kPer;
         int32_t c[kPer];
         int64_t sum = 0;

@@ -2,15 +2,15 @@
 // replacement, relabelled to local indices, with its transpose.
 //
 // A hop is three kernels (plus one for the transpose):
-//   1. prepare   one wavefront per destination: map the destination to its
-//                local index and mark it in the destination bitmap, draw its
+//   1. prepare   16, 32 or 64 lanes per destination: map the destination to
+//                its local index and mark it in the destination map, draw its
 //                sample (Floyd), write the sampled neighbour ids to a padded
-//                [n_dst][k] staging array and mark them in the sample bitmap.
+//                [n_dst][k] staging array and mark them in the sample map.
 //   2. emit      the first workgroups scan the sample counts into the
-//                block's row pointer; the rest walk the bitmaps in vertex
+//                block's row pointer; the rest walk the marks in vertex
 //                order: every vertex that was sampled and is not a
 //                destination becomes the next new source (so new sources
-//                come out in ascending id order); both bitmaps are cleared.
+//                come out in ascending id order); both maps are cleared.
 //   3. relabel   one thread per staged sample: local index via the map
 //                (and, for a block with a transpose, the count phase of the
 //                transpose).
@@ -24,10 +24,10 @@
 // Device workspace (sampler_ws_bytes):
 //   map   int32[graph_n]   vertex -> local source index (valid only for the
 //                          vertices of the current block)
-//   bits  uint32[W]        one bit per vertex: "sampled"
-//   dbits uint32[W]        one bit per vertex: "destination"
+//   bits  one mark per vertex: "sampled" (a byte or a bit, byte_marks)
+//   dbits one mark per vertex: "destination"
 //   ... per-call scratch
-// Both bitmaps are all zero between calls; each call clears the words it set.
+// Both mark maps are all zero between calls; each call clears what it set.
 #include <atomic>
 
 #include "csc_dev.h"
@@ -58,12 +58,7 @@ __global__ void fill_i32_kernel(int32_t *p, int64_t n, int32_t v) {
         p[i] = v;
 }
 
-template <int R>
-__global__ void __launch_bounds__(kThreads) hop_prepare_kernel(HopArgs a) {
-    hop_prepare_body<R>(a, blockIdx.x, gridDim.x);
-}
-
-__global__ void __launch_bounds__(kThreads) hop_emit_kernel(HopArgs a) { hop_emit_body(a); }
+__global__ void __launch_bounds__(kThreads) hop_emit_kernel(HopArgs a) { hop_emit_body(a, blockIdx.x); }
 
 __global__ void __launch_bounds__(kThreads) hop_relabel_kernel(HopArgs a) {
     hop_relabel_body(a, blockIdx.x, gridDim.x);
@@ -75,13 +70,20 @@ struct SharedWs {
 };
 SharedWs shared_layout(int64_t graph_n) {
     const int64_t words = ceil_div(graph_n > 0 ? graph_n : 1, 32);
+    const size_t marks = static_cast<size_t>(words) * (graph_n <= kByteMarks ? 32 : 4);
     Carver c(nullptr);
     SharedWs w;
     w.map = c.take(static_cast<size_t>(graph_n > 0 ? graph_n : 1) * 4);
-    w.bits = c.take(static_cast<size_t>(words) * 4);
-    w.dbits = c.take(static_cast<size_t>(words) * 4);
+    w.bits = c.take(marks);
+    w.dbits = c.take(marks);
     w.total = round_up(c.off, 256);
     return w;
+}
+
+// Workgroups of the emit phase's sources role.
+int64_t mark_tiles(int64_t graph_n, int64_t cap_nnz) {
+    const int words = byte_marks(graph_n, cap_nnz) ? kByteWords : kBitWords;
+    return ceil_div(graph_n > 0 ? graph_n : 1, static_cast<int64_t>(kThreads) * 32 * words);
 }
 
 // Per-hop scratch: staged samples, counts, look-back state, transpose.
@@ -89,16 +91,15 @@ struct HopWs {
     size_t gpad, cnt, status, ticket, csc, total;
 };
 HopWs hop_layout(int64_t graph_n, int64_t cap_dst, int32_t fanout) {
-    const int64_t words = ceil_div(graph_n > 0 ? graph_n : 1, 32);
     const int64_t nb_rows = ceil_div(cap_dst > 0 ? cap_dst : 1, kThreads);
-    const int64_t nb_bits = ceil_div(words, kBitTile);
+    const int64_t nb_bits = mark_tiles(graph_n, cap_dst * fanout);
     const int64_t cap_nnz = std::max<int64_t>(cap_dst * fanout, 1);
     Carver c(nullptr);
     HopWs w;
     w.gpad = c.take(static_cast<size_t>(cap_nnz) * 8);
     w.cnt = c.take(static_cast<size_t>(cap_dst > 0 ? cap_dst : 1) * 4);
     w.status = c.take(static_cast<size_t>(nb_rows + nb_bits) * 8);
-    w.ticket = c.take(4);
+    w.ticket = c.take((kTicketStride + 1) * 4);
     w.csc = c.take(block_csc_ws_bytes(src_bound(graph_n, cap_dst, fanout), cap_nnz));
     w.total = round_up(c.off, 256);
     return w;
@@ -224,9 +225,7 @@ samp::HopPlan plan_hop(const gnn_graph *g, const float *gcn_norm, const int64_t 
     a.n_dst_dev = n_dst_dev;
     a.cap_dst = out->cap_dst;
     a.k = fanout;
-    a.seed = seed;
-    a.step = step;
-    a.hop = static_cast<uint64_t>(static_cast<int64_t>(hop));
+    a.key = mix64(mix64(mix64(seed) ^ step) ^ static_cast<uint64_t>(static_cast<int64_t>(hop)));
     a.counts = out->counts;
     a.src_ids = out->src_ids;
     a.brow = out->rowptr;
@@ -235,7 +234,8 @@ samp::HopPlan plan_hop(const gnn_graph *g, const float *gcn_norm, const int64_t 
     a.map = reinterpret_cast<int32_t *>(base + w.map);
     a.bits = reinterpret_cast<uint32_t *>(base + w.bits);
     a.dbits = reinterpret_cast<uint32_t *>(base + w.dbits);
-    a.words = ceil_div(g->n > 0 ? g->n : 1, 32);
+    a.bytes = byte_marks(g->n, out->cap_dst * fanout);
+    a.graph_n = g->n;
     a.gpad = reinterpret_cast<int64_t *>(hbase + hw.gpad);
     a.cnt = reinterpret_cast<int32_t *>(hbase + hw.cnt);
     a.erow = csc ? csc->erow : nullptr;
@@ -249,27 +249,22 @@ samp::HopPlan plan_hop(const gnn_graph *g, const float *gcn_norm, const int64_t 
     a.status = reinterpret_cast<uint64_t *>(hbase + hw.status);
     a.ticket = reinterpret_cast<int *>(hbase + hw.ticket);
     a.nb_rows = ceil_div(out->cap_dst > 0 ? out->cap_dst : 1, kThreads);
-    a.nb_bits = ceil_div(a.words, kBitTile);
-    // one wavefront per destination row, at most 2048 workgroups (8192
-    // wavefronts) striding over the rows: capacity-sized grids would mostly
-    // hold workgroups that read the row count only to exit
-    p.prep_grid = grid_for(std::max<int64_t>(out->cap_dst, 1) * 64, kThreads, 2048);
+    a.nb_bits = mark_tiles(g->n, out->cap_dst * fanout);
+    p.r = fanout <= 16 ? -16 : fanout <= 32 ? -32 : fanout <= 64 ? 1 : fanout <= 128 ? 2 : fanout <= 256 ? 4
+          : fanout <= 512 ? 8 : 16;
+    // at most 2048 workgroups (8192 wavefronts) striding over the rows:
+    // capacity-sized grids would mostly hold workgroups that read the row
+    // count only to exit
+    p.prep_grid = grid_for(std::max<int64_t>(out->cap_dst, 1) * (p.r < 0 ? -p.r : 64), kThreads, 2048);
     p.emit_grid = static_cast<unsigned>(a.nb_rows + a.nb_bits);
     p.relabel_grid = grid_for(std::max<int64_t>(out->cap_dst, 1) * fanout, kThreads, 1 << 16);
-    p.r = fanout <= 64 ? 1 : fanout <= 128 ? 2 : fanout <= 256 ? 4 : fanout <= 512 ? 8 : 16;
     return p;
 }
 
 gnn_status launch_hop_prepare(const samp::HopPlan &p, hipStream_t s) {
-    switch (p.r) {
-        case 1: hop_prepare_kernel<1><<<p.prep_grid, kThreads, 0, s>>>(p.a); break;
-        case 2: hop_prepare_kernel<2><<<p.prep_grid, kThreads, 0, s>>>(p.a); break;
-        case 4: hop_prepare_kernel<4><<<p.prep_grid, kThreads, 0, s>>>(p.a); break;
-        case 8: hop_prepare_kernel<8><<<p.prep_grid, kThreads, 0, s>>>(p.a); break;
-        default: hop_prepare_kernel<16><<<p.prep_grid, kThreads, 0, s>>>(p.a); break;
-    }
-    GNN_LAUNCHED("hop_prepare");
-    return GNN_OK;
+    gnn_status st = GNN_OK;
+    with_prepare_job(p, [&](auto job) { st = launch_job(job, p.prep_grid, s, "hop_prepare"); });
+    return st;
 }
 
 gnn_status launch_hop_emit(const samp::HopPlan &p, hipStream_t s) {

@@ -57,3 +57,47 @@ def test_transpose_sort_tiers(n_dst):
     got, ref = build(rowptr, col, dst, 32)
     for key in ("src_ids", "rowptr", "col", "cscptr", "cscrow"):
         assert np.array_equal(got[key], getattr(ref, key)), key
+
+
+# Fanouts of up to 16 and 32 take 16 and 32 lanes per row, larger ones a
+# wavefront; degrees just above the fanout make most draws meet a value that
+# an earlier draw took, those that gave way among them.
+@pytest.mark.parametrize("fanout", [1, 2, 5, 15, 16, 17, 25, 31, 32, 33, 64, 65])
+def test_sampler_lanes_per_row(fanout):
+    rng = np.random.default_rng(fanout)
+    n = 1500
+    degrees = [0, 1, fanout - 1, fanout, fanout + 1, fanout + 2, fanout + 3, 2 * fanout + 1, 900]
+    rows = [rng.choice(n, size=degrees[v % len(degrees)], replace=False) for v in range(n)]
+    rowptr, col = csr(rows)
+    for n_dst in (1, 2, 3, 4, 5, 63, 1021):
+        dst = rng.permutation(n)[:n_dst].astype(np.int64)
+        got, ref = build(rowptr, col, dst, fanout, norm=True)
+        for key in ("src_ids", "rowptr", "col", "cscptr", "cscrow"):
+            assert np.array_equal(got[key], getattr(ref, key)), (n_dst, key)
+        assert np.array_equal(got["src_norm"], oracle.gcn_norm(rowptr)[ref.src_ids]), n_dst
+
+
+# A hop that may mark an eighth of the vertices marks them in bytes, else in
+# bits; the last vertices sit at the end of the padded maps.
+@pytest.mark.parametrize("n", [31, 32, 33, 8191, 8192, 8193, 70_000, 300_000])
+def test_sampler_vertex_marks(n):
+    rng = np.random.default_rng(n)
+    ids = np.unique(np.concatenate([[0, n - 1], rng.integers(0, n, size=min(n, 3000))]))
+    deg = np.zeros(n, dtype=np.int64)
+    deg[ids] = rng.integers(0, 12, size=ids.size)
+    rowptr = np.zeros(n + 1, dtype=np.int64)
+    rowptr[1:] = np.cumsum(deg)
+    col = rng.integers(max(0, n - 20_000), n, size=int(rowptr[-1])).astype(np.int64)
+    for v in ids:
+        col[rowptr[v]:rowptr[v + 1]].sort()
+    dst = rng.permutation(ids).astype(np.int64)
+    g = gnn.DeviceGraph(torch.from_numpy(rowptr).to(DEV), torch.from_numpy(col).to(DEV))
+    ws = gnn.sampler_workspace(n, dst.size, 7, DEV)
+    # hops of both kinds share the maps, each meeting what the last one cleared
+    for step, m in enumerate([dst.size, min(dst.size, n // 60 + 1), dst.size]):
+        blk = gnn.DeviceBlock(n, m, 7, True, False, DEV)
+        gnn.build_block(g, torch.from_numpy(dst[:m]).to(DEV), 7, 1, step, 1, blk, ws)
+        torch.cuda.synchronize()
+        got, ref = blk.host(), oracle.build_block(rowptr, col, dst[:m], 7, 1, step, 1)
+        for key in ("src_ids", "rowptr", "col", "cscptr", "cscrow"):
+            assert np.array_equal(got[key], getattr(ref, key)), (step, key)
