@@ -6,11 +6,11 @@
 // work, so the transpose costs no launch of its own:
 //   count  per-column edge counts (atomic increments; done by the relabel of
 //          the hop, which produces the edges' columns, into counters that
-//          the hop's prepare cleared)
+//          the hop's prepare cleared), each edge keeping its number in its
+//          column (the order inside a column is arbitrary here)
 //   scan   column pointers: exclusive scan of the counts, single pass with
-//          ticket-ordered look-back; clears the counters again
-//   place  every edge to a slot of its column (atomic slot counter: the
-//          order inside a column is arbitrary here)
+//          ticket-ordered look-back
+//   place  every edge to its slot of its column
 //   sort   every column in ascending row order, which makes the result
 //          unique: columns of up to kShort entries by one lane with a
 //          sorting network, longer ones by a wavefront, the longest by the
@@ -37,6 +37,7 @@ struct Args {
     int64_t *counts;         // block counts: n_dst, n_src, nnz, error flag
     const int32_t *bcol;     // [nnz] column (local source) of each edge
     int32_t *erow;           // [cap_nnz] row of each edge; scratch of the sort
+    int32_t *eslot;          // [cap_nnz] number of each edge in its column
     int64_t cap_src, cap_nnz;
     int32_t *cnt;            // [cap_src] per-column counters
     uint64_t *status;        // [nb_scan] look-back words
@@ -78,7 +79,6 @@ struct ScanJob {
         for (int q = 0; q < kPer; ++q) {
             const int64_t j = jt + q;
             if (j <= n_src) a.cscptr[j] = run;
-            if (j < n_src) a.cnt[j] = 0;
             run += c[q];
         }
     }
@@ -95,8 +95,8 @@ struct PlaceJob {
                 samp::flag_error(&a.counts[3], samp::kErrRange);
                 continue;
             }
-            const int64_t p = a.cscptr[c] + atomicAdd(&a.cnt[c], 1);
-            if (p < 0 || p >= nnz || p >= a.cscptr[c + 1]) {
+            const int64_t beg = a.cscptr[c], p = beg + a.eslot[e];
+            if (beg < 0 || p < beg || p >= nnz || p >= a.cscptr[c + 1]) {
                 samp::flag_error(&a.counts[3], samp::kErrRange);
                 continue;
             }

@@ -111,9 +111,9 @@ unsigned grid_for(int64_t items, int threads, int64_t max_blocks = 1 << 20) {
     return static_cast<unsigned>(b);
 }
 
-// Transpose scratch: edge rows, column counters, scan look-back state.
+// Transpose scratch: edge rows and slots, column counters, scan look-back state.
 struct CscWs {
-    size_t erow, cnt, status, ticket, total;
+    size_t erow, eslot, cnt, status, ticket, total;
     int64_t nb_scan;
 };
 CscWs csc_layout(int64_t cap_src, int64_t cap_nnz) {
@@ -121,6 +121,7 @@ CscWs csc_layout(int64_t cap_src, int64_t cap_nnz) {
     w.nb_scan = ceil_div(cap_src + 1, csc::kScanTile);
     Carver c(nullptr);
     w.erow = c.take(static_cast<size_t>(std::max<int64_t>(cap_nnz, 1)) * 4);
+    w.eslot = c.take(static_cast<size_t>(std::max<int64_t>(cap_nnz, 1)) * 4);
     w.cnt = c.take(static_cast<size_t>(std::max<int64_t>(cap_src, 1)) * 4);
     w.status = c.take(static_cast<size_t>(w.nb_scan) * 8);
     w.ticket = c.take(4);
@@ -145,6 +146,7 @@ csc::Args csc_args(const gnn_block *out, void *csc_ws, int64_t ws_src, int64_t w
     a.counts = out->counts;
     a.bcol = out->col;
     a.erow = reinterpret_cast<int32_t *>(base + w.erow);
+    a.eslot = reinterpret_cast<int32_t *>(base + w.eslot);
     a.cap_src = std::min(out->cap_src, ws_src);
     a.cap_nnz = std::min(out->cap_nnz, ws_nnz);
     a.cnt = reinterpret_cast<int32_t *>(base + w.cnt);
@@ -239,6 +241,7 @@ samp::HopPlan plan_hop(const gnn_graph *g, const float *gcn_norm, const int64_t 
     a.gpad = reinterpret_cast<int64_t *>(hbase + hw.gpad);
     a.cnt = reinterpret_cast<int32_t *>(hbase + hw.cnt);
     a.erow = csc ? csc->erow : nullptr;
+    a.eslot = csc ? csc->eslot : nullptr;
     a.csc_cnt = csc ? csc->cnt : nullptr;
     a.csc_cap_src = csc ? csc->cap_src : 0;
     a.csc_status = csc ? csc->status : nullptr;
