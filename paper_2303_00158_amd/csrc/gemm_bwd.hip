@@ -25,7 +25,7 @@ __global__ void __launch_bounds__(256) shadow_sync_kernel(const float *__restric
 size_t update_bwd_ws_bytes(int64_t k, int64_t n_out, int64_t cap_m, int gemm_dt) {
     const gbwd::DwPlan p = gbwd::plan_dw(k, n_out, cap_m, gemm_dt == GNN_BF16);
     size_t bytes = round_up(gbwd::dw_part_bytes(p, k, n_out), 256);
-    if (gbwd::wide_bwd_shape(k, n_out, gemm_dt))
+    if (gbwd::wide_bwd_shape(k, n_out, cap_m, gemm_dt))
         bytes = std::max(bytes, static_cast<size_t>(gbwd::plan_wide_bwd(k, n_out, cap_m).ws_bytes));
     return bytes;
 }

@@ -275,7 +275,7 @@ struct WideBwdPlan {
 };
 WideBwdPlan plan_wide_bwd(int64_t K, int64_t n_out, int64_t cap_m);
 // Shapes the wide path may take (the workspace is sized for them) ...
-bool wide_bwd_shape(int64_t K, int64_t n_out, int gemm_dt);
+bool wide_bwd_shape(int64_t K, int64_t n_out, int64_t cap_m, int gemm_dt);
 // ... and calls it takes: bf16 activations, a K tile in one half of
 // [a_self || a_nbr], 32-bit buffer offsets, aligned operands.
 bool wide_bwd_ok(const Args &a);

@@ -28,8 +28,8 @@
 //  * tiles are dealt to the eight XCDs in contiguous ranges of the
 //    row-major tile order, so the workgroups on one XCD share A rows (and
 //    all of W^T) in that XCD's L2;
-//  * tiles are 224 rows high instead of 256 (wavefronts of 112 x 64) where
-//    that fills the CUs' last round better: the kernel's time goes by
+//  * tiles are 224 or 192 rows high instead of 256 (wavefronts of 112 x 64 or
+//    96 x 64) where that fills the CUs' last round better: the kernel's time goes by
 //    rounds of 256 workgroups, so 476 tiles of 224 rows beat 416 of 256;
 //  * the epilogue stages each wavefront's quadrant through LDS 16 rows at a
 //    time and writes row-contiguous 16-byte (bf16) or 32-byte (fp32)
@@ -369,15 +369,15 @@ bool wide_fwd_ok(const void *a_self, const void *a_nbr, int adt, int64_t k_each,
     const int64_t K = a_nbr ? 2 * k_each : k_each;
     // 32-bit buffer offsets: each operand below 2 GB
     const bool fits = cap_m * k_each * 2 < (int64_t(1) << 31) && n_out * K * 2 < (int64_t(1) << 31);
-    return gemm_dt == GNN_BF16 && adt == GNN_BF16 && wt != nullptr && K >= 512 && n_out >= 512 &&
+    return gemm_dt == GNN_BF16 && adt == GNN_BF16 && wt != nullptr && wide_layer(K, n_out, cap_m) &&
            k_each % kBK == 0 && K % (kStages * kBK) == 0 && n_out % 8 == 0 && fits && aligned(a_self, 16) &&
            aligned(a_nbr, 16) && aligned(wt, 16) && aligned(out, 16);
 }
 
 namespace {
 
-// Tile height and grid: 256 or 224 rows, whichever takes the fewest rows x
-// rounds of the CUs (at 26,624 rows and four column tiles: 416 tiles fill
+// Tile height and grid: 256, 224 or 192 rows, whichever takes the fewest rows
+// x rounds of the CUs (at 26,624 rows and four column tiles: 416 tiles fill
 // 1.6 rounds of 256 CUs, 476 fill 1.9; the shorter tiles finish sooner).
 struct WideGrid {
     int fi;
@@ -387,7 +387,9 @@ WideGrid wide_grid(int64_t cap_m, int64_t n_out) {
     WideGrid g{};
     g.tiles_n = ceil_div(n_out, kTile);
     auto cost = [&](int64_t tm) { return ceil_div(ceil_div(cap_m, tm) * g.tiles_n, kCus) * tm; };
-    g.fi = cost(224) < cost(256) ? 7 : 8;
+    g.fi = 8;
+    for (int fi : {7, 6})
+        if (cost(32 * fi) < cost(32 * g.fi)) g.fi = fi;
     g.tiles_m = ceil_div(cap_m, int64_t(32 * g.fi));
     g.per_xcd = ceil_div(g.tiles_m * g.tiles_n, kXcds);
     g.blocks = g.per_xcd * kXcds;
@@ -429,17 +431,19 @@ gnn_status launch_wide_fwd(const void *a_self, const void *a_nbr, int64_t k_each
     // none).  A row count known here (cap_m) never leaves room for a split:
     // the grid has no more workgroups than tiles.
     const int64_t tm_rows = 32 * g.fi;
-    const bool split = ws && m_dev;
+    // Layers that only tall mini-batches bring here (wide_layer) do not split.
+    const bool split = ws && m_dev && wide_shape(p.K, n_out);
     p.part = split ? static_cast<float *>(ws) : nullptr;
     constexpr int NT = Layout<kWideWaves>::kThreads;
     const unsigned gb = static_cast<unsigned>(g.blocks);
-    if (odt == GNN_BF16) {
-        if (g.fi == 8) wide_fwd_kernel<kWideWaves, 8, uint16_t><<<gb, NT, 0, s>>>(p);
-        else wide_fwd_kernel<kWideWaves, 7, uint16_t><<<gb, NT, 0, s>>>(p);
-    } else {
-        if (g.fi == 8) wide_fwd_kernel<kWideWaves, 8, float><<<gb, NT, 0, s>>>(p);
-        else wide_fwd_kernel<kWideWaves, 7, float><<<gb, NT, 0, s>>>(p);
-    }
+    auto go = [&](auto out_tag) {
+        using TO = decltype(out_tag);
+        if (g.fi == 8) wide_fwd_kernel<kWideWaves, 8, TO><<<gb, NT, 0, s>>>(p);
+        else if (g.fi == 7) wide_fwd_kernel<kWideWaves, 7, TO><<<gb, NT, 0, s>>>(p);
+        else wide_fwd_kernel<kWideWaves, 6, TO><<<gb, NT, 0, s>>>(p);
+    };
+    if (odt == GNN_BF16) go(uint16_t{});
+    else go(float{});
     GNN_LAUNCHED("update_fwd_wide");
     if (split) {
         const unsigned rg = static_cast<unsigned>(std::min<int64_t>(ceil_div(cap_m * (n_out / 8), int64_t(256)), 512));

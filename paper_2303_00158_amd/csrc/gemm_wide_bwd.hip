@@ -519,7 +519,13 @@ WideBwdPlan plan_wide_bwd(int64_t K, int64_t n_out, int64_t cap_m) {
     p.k_tiles = ceil_div(K, int64_t(kTile));
     p.tiles = p.k_tiles * ceil_div(n_out, int64_t(kTile));
     const int64_t nch = std::max<int64_t>(ceil_div(cap_m, int64_t(kBK)), 1);
-    const int64_t max_split = std::max<int64_t>(1, std::min<int64_t>({kCus / p.tiles, 64, nch}));
+    int64_t max_split = std::min<int64_t>({kCus / p.tiles, 64, nch});
+    // The partials of layers that only tall mini-batches bring here stay
+    // within the allocation-free entry's scratch, as the engine's did.
+    if (!wide_shape(K, n_out))
+        max_split = std::min<int64_t>(max_split, (GNN_UPDATE_BWD_NOALLOC_MAX_SCRATCH - 256 - wb_bytes(K, n_out)) /
+                                                     ((K + 1) * part_ld(n_out) * 4));
+    max_split = std::max<int64_t>(max_split, 1);
     // dW alone: one workgroup per CU, as many splits as fill the chip in one wave
     p.nsplit = max_split;
     // dW with dA in the same launch: dW's workgroups take tiles x S CUs for
@@ -546,13 +552,13 @@ WideBwdPlan plan_wide_bwd(int64_t K, int64_t n_out, int64_t cap_m) {
     return p;
 }
 
-bool wide_bwd_shape(int64_t K, int64_t n_out, int gemm_dt) {
-    return gemm_dt == GNN_BF16 && K >= 512 && n_out >= 512 && n_out % 8 == 0 && K % 8 == 0;
+bool wide_bwd_shape(int64_t K, int64_t n_out, int64_t cap_m, int gemm_dt) {
+    return gemm_dt == GNN_BF16 && wide_layer(K, n_out, cap_m) && n_out % 8 == 0 && K % 8 == 0;
 }
 
 bool wide_bwd_ok(const Args &a) {
     const int64_t K = a.K();
-    if (!wide_bwd_shape(K, a.n_out, a.gemm_dt) || a.adt != GNN_BF16 || a.cap_m <= 0) return false;
+    if (!wide_bwd_shape(K, a.n_out, a.cap_m, a.gemm_dt) || a.adt != GNN_BF16 || a.cap_m <= 0) return false;
     if (a.a_nbr && a.k_each % kTile != 0) return false;  // a K tile must lie in one half of [a_self || a_nbr]
     // 32-bit buffer offsets
     const int64_t lim = int64_t(1) << 31;

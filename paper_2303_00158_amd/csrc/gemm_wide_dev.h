@@ -38,6 +38,15 @@ constexpr int kStages = 4;        // LDS ring
 constexpr int kXcds = 8;
 constexpr int kTileElems = kTile * kBK;  // one operand tile of one chunk, bf16 elements
 
+// Layers that always take the wide kernels, and those that tall mini-batches
+// bring here.  K of 256 and less is left to the kernels whose results the
+// two-layer launches reproduce bit for bit.
+inline bool wide_shape(int64_t K, int64_t n_out) { return K >= 512 && n_out >= 512; }
+inline bool wide_layer(int64_t K, int64_t n_out, int64_t cap_m) {
+    if (wide_shape(K, n_out)) return true;
+    return K > 256 && n_out >= 192 && ceil_div(cap_m, kTile) * ceil_div(n_out, kTile) >= 128;
+}
+
 // s_waitcnt immediate: vmcnt(vm) expcnt(7, no wait) lgkmcnt(lgkm)
 constexpr int waitcnt(int vm, int lgkm) { return (vm & 15) | ((vm >> 4) << 14) | 0x70 | ((lgkm & 15) << 8); }
 

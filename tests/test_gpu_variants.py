@@ -101,3 +101,96 @@ def test_sampler_vertex_marks(n):
         got, ref = blk.host(), oracle.build_block(rowptr, col, dst[:m], 7, 1, step, 1)
         for key in ("src_ids", "rowptr", "col", "cscptr", "cscrow"):
             assert np.array_equal(got[key], getattr(ref, key)), (step, key)
+
+
+# Layers with K of more than 256 and n_out of 192 and more take the 256 x 256
+# matrix-core tiles once 128 of them hold rows (32,513 rows at one tile column),
+# else the 64 x 64 and 128 x 128 ones; K % 128 and n_out % 8 keep some out.  The
+# forward's tiles are 192, 224 or 256 rows high.
+@pytest.mark.parametrize("k_each,cat,n_out,cap,rows", [
+    (256, True, 256, 32_513, 32_513), (256, True, 256, 32_512, 32_512), (256, True, 192, 40_000, 33_333),
+    (384, False, 200, 32_600, 32_600), (264, False, 256, 33_000, 33_000), (192, True, 256, 33_000, 32_999),
+    (256, True, 188, 33_000, 33_000), (512, False, 264, 17_000, 16_500), (256, True, 256, 57_000, 57_000)])
+def test_update_tall_layers(k_each, cat, n_out, cap, rows):
+    g = torch.Generator(device=DEV).manual_seed(k_each + n_out + cap)
+    a = [torch.randn((cap, k_each), generator=g, device=DEV).bfloat16() for _ in range(2 if cat else 1)]
+    grad = torch.randn((cap, n_out), generator=g, device=DEV)
+    K = k_each * len(a)
+    w = torch.randn((K, n_out), generator=g, device=DEV) / K ** 0.5
+    bias = torch.randn(n_out, generator=g, device=DEV)
+    for t in (*a, grad):
+        t[rows:] = float("nan")  # never part of a result
+    m_dev = torch.tensor([rows], dtype=torch.int64, device=DEV) if rows < cap else None
+    wt = w.t().contiguous().bfloat16()
+    out = torch.zeros((cap, n_out), dtype=torch.bfloat16, device=DEV)
+    dw, db = torch.empty((K, n_out), device=DEV), torch.empty(n_out, device=DEV)
+    da = torch.zeros((cap, K), device=DEV)
+    nbr = a[1] if cat else None
+    gnn.update_fwd(a[0], nbr, w, bias, out, True, gnn.GNN_BF16, m_dev=m_dev, wt=wt)
+    ws = torch.full_like(gnn.update_bwd_workspace(K, n_out, cap, gnn.GNN_BF16, DEV), 255)  # NaN patterns
+    gnn.update_bwd(a[0], nbr, w, grad, dw, db, da, gnn.GNN_BF16, m_dev=m_dev, ws=ws)
+    da_only, dw2, db2 = da.clone(), torch.empty_like(dw), torch.empty_like(db)
+    gnn.update_bwd(a[0], nbr, w, grad, dw2, db2, None, gnn.GNN_BF16, m_dev=m_dev, ws=ws)
+    torch.cuda.synchronize()
+    A = torch.cat([x[:rows] for x in a], 1).double()
+    W, G = w.bfloat16().double(), grad[:rows].bfloat16().double()
+    # 2-norm, relative: fp32 sums of n terms walk off by about 2^-24 sqrt(n)
+    # (4 x for the spread); the bf16 result adds its rounding, at most 2^-9
+    u = 2.0 ** -24
+    for got, want, tol in ((out[:rows], (A @ W + bias.double()).clamp(min=0), 2.0 ** -9 + 4 * u * K ** 0.5),
+                           (dw, A.t() @ G, 4 * u * rows ** 0.5), (dw2, A.t() @ G, 4 * u * rows ** 0.5),
+                           (db, grad[:rows].double().sum(0), 4 * u * rows ** 0.5),
+                           (da_only[:rows], G @ W.t(), 4 * u * n_out ** 0.5)):
+        assert float((got.double() - want).norm() / want.norm()) <= tol
+    # (with and without dA the rows may be split differently: db2 has its own sums)
+    assert float((db2.double() - db.double()).norm() / db.double().norm()) <= 8 * u * rows ** 0.5
+    # the entry that brings its own scratch gives the same bits for every size it took
+    if ws.numel() <= 32 << 20:
+        dw3, db3, da3 = torch.empty_like(dw), torch.empty_like(db), torch.zeros_like(da)
+        gnn.update_bwd_noalloc(a[0], nbr, w, grad, dw3, db3, da3, gnn.GNN_BF16, m_dev=m_dev)
+        assert torch.equal(dw3, dw) and torch.equal(db3, db) and torch.equal(da3[:rows], da[:rows])
+    else:
+        assert K >= 512 and n_out >= 512
+
+
+# Transpose columns of more than 16 entries are summed by the workgroup, the
+# first 64 of them per workgroup; repeated entries, several 64-entry windows,
+# widths from one lane to more than a workgroup.
+@pytest.mark.parametrize("f", [1, 32, 63, 100, 130, 256, 260, 300])
+@pytest.mark.parametrize("kind", ["mean", "gcn", "max"])
+def test_aggregate_bwd_long_columns(kind, f):
+    from tests.test_gpu_parity import relerr, upload_block
+    rng = np.random.default_rng(f)
+    n_dst, n_src = 700, 900
+    lens = np.concatenate([[0, 1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 699, 700], rng.integers(1, 30, size=n_src - 13)])
+    rows = [[] for _ in range(n_dst)]
+    for c, l in enumerate(lens):
+        for v in rng.choice(n_dst, size=l, replace=False):
+            rows[v].append(c)
+    for v in range(0, n_dst, 3):
+        rows[v] += rows[v][:2]
+    rowptr = np.zeros(n_dst + 1, dtype=np.int64)
+    rowptr[1:] = np.cumsum([len(r) for r in rows])
+    col = np.concatenate([np.array(r, dtype=np.int32) for r in rows])
+    row_of = np.repeat(np.arange(n_dst, dtype=np.int32), np.diff(rowptr))
+    order = np.argsort(col, kind="stable")
+    cscptr = np.zeros(n_src + 1, dtype=np.int64)
+    cscptr[1:] = np.cumsum(np.bincount(col, minlength=n_src))
+    blk = oracle.Block(src_ids=np.arange(n_src, dtype=np.int64), rowptr=rowptr, col=col, cscptr=cscptr,
+                       cscrow=row_of[order].astype(np.int32), n_dst=n_dst)
+    norm = rng.uniform(0.1, 1, size=n_src).astype(np.float32) if kind == "gcn" else None
+    b = upload_block(blk, norm)
+    d_a = rng.standard_normal((n_dst, f if kind == "gcn" else 2 * f)).astype(np.float32)
+    h = rng.standard_normal((n_src, f)).astype(np.float32)
+    d_src = torch.empty((n_src, f), device=DEV)
+    d_a_d, h_d = torch.from_numpy(d_a).to(DEV), torch.from_numpy(h).to(DEV)
+    if kind == "max":
+        _, arg = oracle.aggregate_fwd_max(blk, h, oracle.F32)
+        want = oracle.aggregate_bwd_max(blk, arg, d_a, f, h, oracle.F64)
+        gnn.aggregate_bwd_max(b, torch.from_numpy(arg).to(DEV), d_a_d, f, d_src, h_d)
+    else:
+        ok, gk = (oracle.GCN, gnn.GNN_AGG_GCN_SYM) if kind == "gcn" else (oracle.SAGE, gnn.GNN_AGG_SAGE_MEAN)
+        want = oracle.aggregate_bwd(ok, blk, norm, d_a, f, h, oracle.F64)
+        gnn.aggregate_bwd(b, gk, d_a_d, f, d_src, h_d)
+    # fp32 sums of up to 900 terms: within 900 2^-24 of the terms' magnitude sum
+    assert relerr(d_src.cpu().numpy(), want) <= 1e-5
