@@ -170,14 +170,13 @@ __device__ __forceinline__ void agg_fwd_row(const int64_t *__restrict__ rowptr, 
 // ---------------------------------------------------------------------------
 template <int KIND, class THB, bool VEC>
 __device__ __forceinline__ void agg_bwd_row(int64_t n_dst, const int64_t *__restrict__ rowptr,
-                                            const int64_t *__restrict__ cscptr, const int32_t *__restrict__ cscrow,
+                                            const int32_t *__restrict__ cscrow,
                                             const float *__restrict__ src_norm, const float *__restrict__ d_a,
                                             int64_t f, int C, int S, const THB *__restrict__ h_below,
-                                            float *__restrict__ d_src, int64_t j) {
+                                            float *__restrict__ d_src, int64_t j, int64_t beg, int64_t end) {
     const int lane = threadIdx.x & 63;
     const int64_t ka = (KIND == GNN_AGG_SAGE_MEAN) ? 2 * f : f;
     const int64_t nbr_off = (KIND == GNN_AGG_SAGE_MEAN) ? f : 0;
-    const int64_t beg = cscptr[j], end = cscptr[j + 1];
     const float wj = (KIND == GNN_AGG_GCN_SYM) ? src_norm[j] : 1.f;
     const int groups = (C + 63) / 64;
     const int slot = (S > 1) ? lane / C : 0;
@@ -227,6 +226,76 @@ __device__ __forceinline__ void agg_bwd_row(int64_t n_dst, const int64_t *__rest
             if (!(hb.w > 0.f)) acc.w = 0.f;
         }
         store_chunk<VEC>(d_src, j * f, e0, f, acc);
+    }
+}
+
+// The transpose's long columns (the graph's hubs): a wavefront that walks one
+// alone, four edges in flight, is still at it when the rest of the grid has
+// finished. Such columns are put aside (LongColumns) and summed by the
+// whole workgroup afterwards, a thread per element and kLongAhead edges in
+// flight, the edges in the same sequence (for rows of more than 128 elements,
+// whose wavefronts walk all edges in sequence, the sums are the same bit for
+// bit). At 8,192 targets (fanout 25, f = 256; the longest column has about 180
+// of the 59k edges) the mean's backward took 36 us, now 32, the
+// maximum's 79 us, now 43.
+constexpr int kLong = 16;       // longest column of one wavefront
+constexpr int kLongAhead = 16;
+struct LongColumns {
+    static constexpr int kCap = 64;  // columns past it stay with their wavefronts
+    int n;
+    int32_t j[kCap];
+    // One wavefront: put column c (uniform) aside; false when there is no room.
+    __device__ __forceinline__ bool add(int64_t c) {
+        int at = 0;
+        if ((threadIdx.x & 63) == 0) {
+            at = atomicAdd(&n, 1);
+            if (at < kCap) j[at] = static_cast<int32_t>(c);
+        }
+        return __builtin_amdgcn_readfirstlane(at) < kCap;
+    }
+};
+
+template <int KIND, class THB>
+__device__ __forceinline__ void agg_bwd_long(int64_t n_dst, const int64_t *__restrict__ rowptr,
+                                             const int32_t *__restrict__ cscrow, const float *__restrict__ src_norm,
+                                             const float *__restrict__ d_a, int64_t f, const THB *__restrict__ h_below,
+                                             float *__restrict__ d_src, int64_t j, int64_t beg, int64_t end) {
+    const int lane = threadIdx.x & 63;
+    const int64_t ka = (KIND == GNN_AGG_SAGE_MEAN) ? 2 * f : f;
+    const int64_t nbr_off = (KIND == GNN_AGG_SAGE_MEAN) ? f : 0;
+    const float wj = (KIND == GNN_AGG_GCN_SYM) ? src_norm[j] : 1.f;
+    // a wavefront past the row has nothing to add (e0 is uniform in it)
+    for (int64_t e0 = threadIdx.x - lane; e0 < f; e0 += kThreads) {
+        const int64_t e = min(e0 + lane, f - 1);
+        const float self = d_a[(j < n_dst ? j : 0) * ka + e];
+        const float hb = h_below ? Elem<THB>::load(h_below, j * f + e) : 1.f;
+        float acc = 0.f;
+        for (int64_t wb = beg; wb < end; wb += 64) {
+            const int wn = static_cast<int>(min<int64_t>(64, end - wb));
+            int32_t my_idx = 0;
+            float my_w = 0.f;
+            if (lane < wn) {
+                my_idx = cscrow[wb + lane];
+                if (KIND == GNN_AGG_GCN_SYM)
+                    my_w = src_norm[my_idx] * wj;
+                else
+                    my_w = 1.f / static_cast<float>(rowptr[my_idx + 1] - rowptr[my_idx]);
+            }
+            for (int tb = 0; tb < wn; tb += kLongAhead) {
+                float v[kLongAhead], w[kLongAhead];
+#pragma unroll
+                for (int u = 0; u < kLongAhead; ++u) {  // (lanes past the window hold row 0 with weight 0)
+                    const int64_t i = __builtin_amdgcn_readlane(my_idx, tb + u);
+                    w[u] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), tb + u));
+                    v[u] = d_a[i * ka + nbr_off + e];
+                }
+#pragma unroll
+                for (int u = 0; u < kLongAhead; ++u) acc = fmaf(w[u], tb + u < wn ? v[u] : 0.f, acc);
+            }
+        }
+        if (j < n_dst) acc = fmaf((KIND == GNN_AGG_GCN_SYM) ? wj * wj : 1.f, self, acc);
+        if (!(hb > 0.f)) acc = 0.f;
+        if (e0 + lane < f) d_src[j * f + e] = acc;
     }
 }
 
@@ -345,10 +414,22 @@ struct BwdJob {
     const THB *h_below;
     float *d_src;
     __device__ void run(int64_t blk, int64_t nblk) const {
+        __shared__ LongColumns aside;
         const int64_t n_dst = b.counts[0], n_src = b.counts[1];
-        for (int64_t j = blk * kWaves + (threadIdx.x >> 6); j < n_src; j += nblk * kWaves)
-            agg_bwd_row<KIND, THB, VEC>(n_dst, b.rowptr, b.cscptr, b.cscrow, b.src_norm, d_a, f, C, S, h_below,
-                                        d_src, j);
+        if (threadIdx.x == 0) aside.n = 0;
+        __syncthreads();
+        for (int64_t j = blk * kWaves + (threadIdx.x >> 6); j < n_src; j += nblk * kWaves) {
+            const int64_t beg = b.cscptr[j], end = b.cscptr[j + 1];
+            if (end - beg > kLong && aside.add(j)) continue;
+            agg_bwd_row<KIND, THB, VEC>(n_dst, b.rowptr, b.cscrow, b.src_norm, d_a, f, C, S, h_below, d_src, j, beg,
+                                        end);
+        }
+        __syncthreads();
+        for (int i = 0; i < min(aside.n, LongColumns::kCap); ++i) {
+            const int64_t j = aside.j[i];
+            agg_bwd_long<KIND, THB>(n_dst, b.rowptr, b.cscrow, b.src_norm, d_a, f, h_below, d_src, j, b.cscptr[j],
+                                    b.cscptr[j + 1]);
+        }
     }
 };
 
@@ -471,14 +552,12 @@ __device__ __forceinline__ void agg_fwd_row_max(const int64_t *__restrict__ rowp
 // first of them counts: the maximum passes its gradient once.  The
 // neighbour rows of d_a are read only for elements that j won.
 template <class THB, bool VEC>
-__device__ __forceinline__ void agg_bwd_row_max(int64_t n_dst, const int64_t *__restrict__ cscptr,
-                                                const int32_t *__restrict__ cscrow, const int32_t *__restrict__ argmax,
-                                                const float *__restrict__ d_a, int64_t f, int C, int S,
-                                                const THB *__restrict__ h_below, float *__restrict__ d_src,
-                                                int64_t j) {
+__device__ __forceinline__ void agg_bwd_row_max(int64_t n_dst, const int32_t *__restrict__ cscrow,
+                                                const int32_t *__restrict__ argmax, const float *__restrict__ d_a,
+                                                int64_t f, int C, int S, const THB *__restrict__ h_below,
+                                                float *__restrict__ d_src, int64_t j, int64_t beg, int64_t end) {
     const int lane = threadIdx.x & 63;
     const int64_t ka = 2 * f;
-    const int64_t beg = cscptr[j], end = cscptr[j + 1];
     const int32_t jj = static_cast<int32_t>(j);
     const int groups = (C + 63) / 64;
     const int slot = (S > 1) ? lane / C : 0;
@@ -552,6 +631,56 @@ __device__ __forceinline__ void agg_bwd_row_max(int64_t n_dst, const int64_t *__
     }
 }
 
+// A long column of the maximum's backward, by the whole workgroup
+// (agg_bwd_long's split and order). Elements that j did not win read the
+// self part's element instead of their row's (a line that is at hand), so that
+// a batch's loads need no branches.
+template <class THB>
+__device__ __forceinline__ void agg_bwd_long_max(int64_t n_dst, const int32_t *__restrict__ cscrow,
+                                                 const int32_t *__restrict__ argmax, const float *__restrict__ d_a,
+                                                 int64_t f, const THB *__restrict__ h_below,
+                                                 float *__restrict__ d_src, int64_t j, int64_t beg, int64_t end) {
+    const int lane = threadIdx.x & 63;
+    const int64_t ka = 2 * f;
+    const int32_t jj = static_cast<int32_t>(j);
+    for (int64_t e0 = threadIdx.x - lane; e0 < f; e0 += kThreads) {
+        const int64_t e = min(e0 + lane, f - 1), self_at = (j < n_dst ? j : 0) * ka + e;
+        const float self = d_a[self_at];
+        const float hb = h_below ? Elem<THB>::load(h_below, j * f + e) : 1.f;
+        float acc = 0.f;
+        for (int64_t wb = beg; wb < end; wb += 64) {
+            const int wn = static_cast<int>(min<int64_t>(64, end - wb));
+            // a row's second and later entries count as no row (-1)
+            int32_t my_idx = -1;
+            if (lane < wn) {
+                my_idx = cscrow[wb + lane];
+                if (wb + lane > beg && cscrow[wb + lane - 1] == my_idx) my_idx = -1;
+            }
+            for (int tb = 0; tb < wn; tb += kLongAhead) {
+                int32_t a[kLongAhead];
+                float v[kLongAhead];
+#pragma unroll
+                for (int u = 0; u < kLongAhead; ++u) {
+                    const int64_t i = __builtin_amdgcn_readlane(my_idx, tb + u);
+                    a[u] = argmax[(i < 0 ? 0 : i) * f + e];
+                }
+#pragma unroll
+                for (int u = 0; u < kLongAhead; ++u) {
+                    const int64_t i = __builtin_amdgcn_readlane(my_idx, tb + u);
+                    const bool won = i >= 0 && a[u] == jj;
+                    const float x = d_a[won ? i * ka + f + e : self_at];
+                    v[u] = won ? x : 0.f;
+                }
+#pragma unroll
+                for (int u = 0; u < kLongAhead; ++u) acc += v[u];
+            }
+        }
+        if (j < n_dst) acc += self;
+        if (!(hb > 0.f)) acc = 0.f;
+        if (e0 + lane < f) d_src[j * f + e] = acc;
+    }
+}
+
 template <class TIn, class TOut, bool VEC>
 struct FwdMaxJob {
     gnn_block b;
@@ -577,9 +706,20 @@ struct BwdMaxJob {
     const THB *h_below;
     float *d_src;
     __device__ void run(int64_t blk, int64_t nblk) const {
+        __shared__ LongColumns aside;
         const int64_t n_dst = b.counts[0], n_src = b.counts[1];
-        for (int64_t j = blk * kWaves + (threadIdx.x >> 6); j < n_src; j += nblk * kWaves)
-            agg_bwd_row_max<THB, VEC>(n_dst, b.cscptr, b.cscrow, argmax, d_a, f, C, S, h_below, d_src, j);
+        if (threadIdx.x == 0) aside.n = 0;
+        __syncthreads();
+        for (int64_t j = blk * kWaves + (threadIdx.x >> 6); j < n_src; j += nblk * kWaves) {
+            const int64_t beg = b.cscptr[j], end = b.cscptr[j + 1];
+            if (end - beg > kLong && aside.add(j)) continue;
+            agg_bwd_row_max<THB, VEC>(n_dst, b.cscrow, argmax, d_a, f, C, S, h_below, d_src, j, beg, end);
+        }
+        __syncthreads();
+        for (int i = 0; i < min(aside.n, LongColumns::kCap); ++i) {
+            const int64_t j = aside.j[i];
+            agg_bwd_long_max<THB>(n_dst, b.cscrow, argmax, d_a, f, h_below, d_src, j, b.cscptr[j], b.cscptr[j + 1]);
+        }
     }
 };
 
