@@ -2,12 +2,12 @@
 // CSR) and backward (pull over its transpose, no atomics): the mean and GCN
 // sums, and GraphSAGE's max aggregator with its argmax table.
 //
-// Work split: one wavefront per output row.  A row of f elements is cut into
-// C = ceil(f / 4) chunks of 4; when C <= 32 the wavefront is divided into
-// S = 64 / C slots that walk different edges of the row at once (f = 100:
-// two slots of 25 lanes), and the slot partial sums are folded with lane
-// shuffles at the end.  Up to 64 neighbour indices and weights of the row are
-// held one per lane and broadcast with shuffles.  Sums are fp32.
+// Work split: one wavefront per output row (the forward sums: up to two).  A
+// row of f elements is cut into C = ceil(f / 4) chunks of 4; when C <= 32 the
+// wavefront is divided into S = 64 / C slots that walk different edges of the
+// row at once (f = 100: two slots of 25 lanes), and the slot partial sums are
+// folded with lane shuffles at the end.  The backward walks a source's edges
+// in sequence, several sources per wavefront for narrow rows.  Sums are fp32.
 #pragma once
 
 #include <math.h>
@@ -65,156 +65,249 @@ __device__ __forceinline__ float4 shfl4(const float4 &v, int src) {
     return make_float4(__shfl(v.x, src, 64), __shfl(v.y, src, 64), __shfl(v.z, src, 64), __shfl(v.w, src, 64));
 }
 
-// Accumulate sum_{t in this lane's slot} w_t * x[idx_t][chunk] over one
-// window of up to 64 (index, weight) pairs held one per lane.  Every lane runs
-// the same number of iterations so the shuffles stay convergent.  Lanes past
-// the window hold index 0 (a valid row) and the loads are issued
-// unconditionally; invalid terms are masked to zero before the FMA.  The
-// caller passes an in-row chunk offset for inactive lanes.  ROUND: every
-// loaded value is first rounded to bf16 (round to nearest even), so that
-// summing fp32 table rows gives exactly the sum over their bf16 copies.
 __device__ __forceinline__ float4 round_bf16(float4 v) {
     return make_float4(bf16_to_f32(f32_to_bf16(v.x)), bf16_to_f32(f32_to_bf16(v.y)), bf16_to_f32(f32_to_bf16(v.z)),
                        bf16_to_f32(f32_to_bf16(v.w)));
 }
-template <bool VEC, class T, bool ROUND = false>
-__device__ __forceinline__ void window_accumulate(float4 &acc, const T *x, int64_t stride, int64_t col_off,
-                                                  int64_t f, int32_t my_idx, float my_w, int wn, int slot, int S,
-                                                  bool active, int64_t e0) {
-    for (int tb = 0; tb < wn; tb += 4 * S) {
-        int32_t j[4];
-        float w[4];
-        bool ok[4];
+// ---------------------------------------------------------------------------
+// forward
+//
+// A row is summed by S slots: within a window of 64 edges slot s takes edges s,
+// s + S, ... one after another, and the slots are added in order at the end.
+// S = 64 / ceil(f / 4) (1 when a row has more than 32 chunks of 4) fixes the
+// order of the sums for every kernel that has to reproduce it. A lane holds E
+// consecutive elements of its slot's sum, so a row takes S CL lanes, CL =
+// ceil(f / E), and a wavefront R = 64 / (S CL) rows.
+//
+// The kernel is bound by the misses in flight, so what counts is that its
+// whole grid is resident (at most 64 registers: FwdJob) and that a wavefront
+// covers many edges at once.  bf16 rows use E = 8: one 16-byte
+// load (4-byte aligned; the last lane's is moved back to end with the row)
+// instead of two, two rows per wavefront for f = 100, and every lane loads the
+// column indices of its own slot's edges instead of taking them from other
+// lanes. 1.19M edges of 32,768 targets, f = 100: 74 us with 4 elements per
+// lane, shuffled indices and 6 wavefronts per SIMD, now 50 us.
+// ---------------------------------------------------------------------------
+
+// E consecutive elements as loaded (add() adds w times their values).
+template <class T, int E, bool VEC, bool ROUND> struct RowElems {
+    float4 v;  // E = 4
+    __device__ __forceinline__ void load(const T *p, int64_t row_off, int64_t e0, int64_t f) {
+        v = load_chunk<VEC>(p, row_off, e0, f);
+    }
+    __device__ __forceinline__ void add(float (&acc)[4], float w) const {
+        const float4 x = ROUND ? round_bf16(v) : v;
+        acc[0] = fmaf(w, x.x, acc[0]);
+        acc[1] = fmaf(w, x.y, acc[1]);
+        acc[2] = fmaf(w, x.z, acc[2]);
+        acc[3] = fmaf(w, x.w, acc[3]);
+    }
+};
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+template <bool VEC, bool ROUND> struct RowElems<uint16_t, 8, VEC, ROUND> {
+    u32x4_a4 v;
+    __device__ __forceinline__ void load(const uint16_t *p, int64_t row_off, int64_t e0, int64_t) {
+        v = *reinterpret_cast<const u32x4_a4 *>(p + row_off + e0);
+    }
+    __device__ __forceinline__ void add(float (&acc)[8], float w) const {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int t = tb + q * S + slot;
-            ok[q] = active && (t < wn);
-            j[q] = __shfl(my_idx, t & 63, 64);
-            w[q] = __shfl(my_w, t & 63, 64);
+        for (int i = 0; i < 4; ++i) {
+            acc[2 * i] = fmaf(w, __uint_as_float(v[i] << 16), acc[2 * i]);
+            acc[2 * i + 1] = fmaf(w, __uint_as_float(v[i] & 0xffff0000u), acc[2 * i + 1]);
         }
-        float4 v[4];
+    }
+};
+template <int E, bool VEC, class T>
+__device__ __forceinline__ void store_elems(T *p, int64_t row_off, int64_t e0, int64_t f, const float (&a)[E]) {
+    if constexpr (E == 4) {
+        store_chunk<VEC>(p, row_off, e0, f, make_float4(a[0], a[1], a[2], a[3]));
+    } else if constexpr (sizeof(T) == 2) {
+        u32x4_a4 o;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            v[q] = load_chunk<VEC>(x, static_cast<int64_t>(j[q]) * stride + col_off, e0, f);
-            if constexpr (ROUND) v[q] = round_bf16(v[q]);
-        }
+        for (int i = 0; i < 4; ++i)
+            o[i] = static_cast<uint32_t>(f32_to_bf16(a[2 * i])) | (static_cast<uint32_t>(f32_to_bf16(a[2 * i + 1])) << 16);
+        *reinterpret_cast<u32x4_a4 *>(p + row_off + e0) = o;
+    } else {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float wq = ok[q] ? w[q] : 0.f;
-            const float4 vq = ok[q] ? v[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-            fma4(acc, wq, vq);
+        for (int h = 0; h < 2; ++h) {
+            u32x4_a4 o;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = __float_as_uint(a[4 * h + i]);
+            *reinterpret_cast<u32x4_a4 *>(p + row_off + e0 + 4 * h) = o;
         }
     }
 }
 
-// ---------------------------------------------------------------------------
-// forward
-// ---------------------------------------------------------------------------
-template <int KIND, class TIn, class TOut, bool VEC>
-__device__ __forceinline__ void agg_fwd_row(const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
-                                            const float *__restrict__ src_norm, const TIn *__restrict__ h, int64_t f,
-                                            int C, int S, TOut *__restrict__ out, int64_t row) {
+// A lane's place in its wavefront's rows.
+struct RowLanes {
+    int r, slot, chunk;
+    bool active;
+    __device__ __forceinline__ RowLanes(int CL, int S, int R) {
+        const int lane = threadIdx.x & 63, per_row = S * CL;
+        if (per_row > 64) {  // one row, a chunk group at a time
+            r = slot = 0;
+            chunk = lane;
+            active = true;
+            return;
+        }
+        r = lane / per_row;
+        slot = lane % per_row / CL;
+        chunk = lane % CL;  // (CL divides per_row)
+        active = r < R;
+    }
+};
+
+// Where a row's edges lie and whose rows they read: a block's own columns and
+// its source rows ...
+template <class TIn> struct BlockEdges {
+    using T = TIn;
+    static constexpr bool kRound = false;
+    const int32_t *col;
+    const float *norm;
+    const TIn *x;
+    int64_t stride;
+    __device__ __forceinline__ int32_t at(int64_t, int64_t beg, int32_t p) const { return col[beg + p]; }
+};
+// ... or an fp32 feature table in device memory (the feature loading fused
+// into the input layer's aggregation): row i's p-th sampled neighbour is the
+// global vertex gids[i k + p] (the sampler's staging of the block, in the
+// block's column order), whose table row is rounded to bf16 element by element,
+// exactly as the gather would have stored it in X'. Same slots and order of
+// summation as over X', so the result is bitwise the same. norm holds the
+// graph's normalisers by global id (src_norm of the block holds the same
+// values).
+struct TableEdges {
+    using T = float;
+    static constexpr bool kRound = true;
+    const int64_t *gids;
+    int64_t k;
+    const float *norm;
+    const float *x;
+    int64_t stride;
+    __device__ __forceinline__ int32_t at(int64_t row, int64_t, int32_t p) const {
+        return static_cast<int32_t>(gids[row * k + p]);  // (graphs of up to 2^31 - 1 vertices)
+    }
+};
+
+// Rows row0 .. row0 + R - 1 of one wavefront. The GCN self term is row i of
+// x_self.
+template <int KIND, int E, bool VEC, class Edges, class TSelf, class TOut>
+__device__ __forceinline__ void agg_fwd_rows(const Edges &edges, const int64_t *__restrict__ rowptr,
+                                             const float *__restrict__ src_norm, const TSelf *__restrict__ x_self,
+                                             int64_t n, int64_t f, int CL, int S, const RowLanes &L,
+                                             TOut *__restrict__ out, int64_t row0) {
+    using T = typename Edges::T;
     const int lane = threadIdx.x & 63;
-    const int64_t beg = rowptr[row], end = rowptr[row + 1];
-    const int64_t deg = end - beg;
+    const bool live = L.active && row0 + L.r < n;
+    const int64_t row = live ? row0 + L.r : row0;
+    const int64_t beg = rowptr[row];
+    const int32_t deg = static_cast<int32_t>(rowptr[row + 1] - beg), mine = live ? deg : 0;
     const float wi = (KIND == GNN_AGG_GCN_SYM) ? src_norm[row] : 1.f;
-    const int groups = (C + 63) / 64;
-    const int slot = (S > 1) ? lane / C : 0;
-    for (int g = 0; g < groups; ++g) {
-        const int chunk = (S > 1) ? lane % C : g * 64 + lane;
-        const bool active = (S > 1) ? (slot < S) : (chunk < C);
-        const int64_t e0 = active ? static_cast<int64_t>(chunk) * 4 : 0;
-        // the GCN self term, issued before the neighbours
-        const float4 self = (KIND == GNN_AGG_GCN_SYM) ? load_chunk<VEC>(h, row * f, e0, f)
-                                                        : make_float4(0.f, 0.f, 0.f, 0.f);
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int64_t wb = beg; wb < end; wb += 64) {
-            const int wn = static_cast<int>(min<int64_t>(64, end - wb));
-            int32_t my_idx = 0;
-            float my_w = 0.f;
-            if (lane < wn) {
-                my_idx = col[wb + lane];
-                my_w = (KIND == GNN_AGG_GCN_SYM) ? wi * src_norm[my_idx] : 1.f;
+    for (int chunk = L.chunk; chunk < CL; chunk += 64) {
+        const int64_t e0 = E == 8 ? min(static_cast<int64_t>(chunk) * 8, f - 8) : static_cast<int64_t>(chunk) * E;
+        RowElems<TSelf, E, VEC, false> self;
+        if (KIND == GNN_AGG_GCN_SYM) self.load(x_self, row * f, e0, f);  // issued before the neighbours
+        float acc[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[e] = 0.f;
+        for (int32_t wb = 0; wb < mine; wb += 64) {
+            const int wn = min(64, mine - wb);
+            for (int t = L.slot; t < wn; t += 4 * S) {
+                int32_t j[4];
+                float w[4];
+                RowElems<T, E, VEC, Edges::kRound> v[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (t + q * S < wn) j[q] = edges.at(row, beg, wb + t + q * S);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (t + q * S < wn) {
+                        w[q] = (KIND == GNN_AGG_GCN_SYM) ? wi * edges.norm[j[q]] : 1.f;
+                        v[q].load(edges.x, static_cast<int64_t>(j[q]) * edges.stride, e0, f);
+                    }
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (t + q * S < wn) v[q].add(acc, w[q]);
             }
-            window_accumulate<VEC>(acc, h, f, 0, f, my_idx, my_w, wn, slot, S, active, e0);
         }
         // fold the slots into slot 0
         for (int s2 = 1; s2 < S; ++s2) {
-            const float4 o = shfl4(acc, lane + s2 * C);
-            if (slot == 0) {
-                acc.x += o.x;
-                acc.y += o.y;
-                acc.z += o.z;
-                acc.w += o.w;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const float o = __shfl(acc[e], lane + s2 * CL, 64);
+                if (L.slot == 0) acc[e] += o;
             }
         }
-        if (slot != 0 || !active) continue;
+        if (L.slot != 0 || !live) continue;
         if (KIND == GNN_AGG_SAGE_MEAN) {
             if (deg > 0) {
                 const float d = static_cast<float>(deg);
-                acc.x /= d;
-                acc.y /= d;
-                acc.z /= d;
-                acc.w /= d;
+#pragma unroll
+                for (int e = 0; e < E; ++e) acc[e] /= d;
             }
         } else {
-            const float ws = wi * wi;
-            fma4(acc, ws, self);
+            self.add(acc, wi * wi);
         }
-        store_chunk<VEC>(out, row * f, e0, f, acc);
+        store_elems<E, VEC>(out, row * f, e0, f, acc);
     }
 }
 
 // ---------------------------------------------------------------------------
 // backward: d_src[j] = self(j) + sum_{i in csc(j)} w_ij d_a[i, nbr part]
+//
+// A source's edges are added one after another, four loads in flight; a row
+// takes ceil(f / 4) lanes, so rows of up to 128 elements share a wavefront
+// (RowLanes). Most sources have one or two edges: the kernel is a chain of
+// three dependent loads per row (column pointer, rows, their gradients), so what
+// counts is that many rows are in flight (8,192 targets, f = 256: 32 us with indices and
+// weights taken from other lanes at 75 registers, now 28 us; the maximum's 43
+// us, now 41).
 // ---------------------------------------------------------------------------
-template <int KIND, class THB, bool VEC>
-__device__ __forceinline__ void agg_bwd_row(int64_t n_dst, const int64_t *__restrict__ rowptr,
-                                            const int32_t *__restrict__ cscrow,
-                                            const float *__restrict__ src_norm, const float *__restrict__ d_a,
-                                            int64_t f, int C, int S, const THB *__restrict__ h_below,
-                                            float *__restrict__ d_src, int64_t j, int64_t beg, int64_t end) {
-    const int lane = threadIdx.x & 63;
+// This lane's column j, its edges beg .. beg + len - 1. UNI: one column per
+// wavefront (C > 32), whose indices are kept scalar.
+template <bool UNI> __device__ __forceinline__ int32_t maybe_scalar(int32_t x) {
+    if constexpr (UNI) return __builtin_amdgcn_readfirstlane(x);
+    return x;
+}
+template <int KIND, class THB, bool VEC, bool UNI>
+__device__ __forceinline__ void agg_bwd_rows(int64_t n_dst, const int64_t *__restrict__ rowptr,
+                                             const int32_t *__restrict__ cscrow, const float *__restrict__ src_norm,
+                                             const float *__restrict__ d_a, int64_t f, int C, const RowLanes &L,
+                                             const THB *__restrict__ h_below, float *__restrict__ d_src, int64_t j,
+                                             int64_t beg, int32_t len) {
     const int64_t ka = (KIND == GNN_AGG_SAGE_MEAN) ? 2 * f : f;
     const int64_t nbr_off = (KIND == GNN_AGG_SAGE_MEAN) ? f : 0;
     const float wj = (KIND == GNN_AGG_GCN_SYM) ? src_norm[j] : 1.f;
-    const int groups = (C + 63) / 64;
-    const int slot = (S > 1) ? lane / C : 0;
-    for (int g = 0; g < groups; ++g) {
-        const int chunk = (S > 1) ? lane % C : g * 64 + lane;
-        const bool active = (S > 1) ? (slot < S) : (chunk < C);
-        const int64_t e0 = active ? static_cast<int64_t>(chunk) * 4 : 0;
+    const bool mask = h_below != nullptr;
+    for (int chunk = L.chunk; chunk < C; chunk += 64) {
+        const uint32_t e0 = static_cast<uint32_t>(chunk) * 4;
         // the self term and the ReLU mask, issued before the neighbours so
-        // that their latency overlaps the sum (a source past the destinations
-        // reads destination row 0, unused; with no mask an in-bounds stand-in
-        // address, unused; THB is float whenever h_below is null)
-        const float4 self = load_chunk<VEC>(d_a, (j < n_dst ? j : 0) * ka, e0, f);
-        const bool mask = h_below != nullptr;
-        const float4 hb = load_chunk<VEC>(mask ? h_below : reinterpret_cast<const THB *>(d_a), mask ? j * f : 0, e0, f);
+        // that their latency overlaps the sum
+        float4 self, hb;
+        if (j < n_dst) self = load_chunk<VEC>(d_a + j * ka, 0, e0, f);
+        if (mask) hb = load_chunk<VEC>(h_below + j * f, 0, e0, f);
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int64_t wb = beg; wb < end; wb += 64) {
-            const int wn = static_cast<int>(min<int64_t>(64, end - wb));
-            int32_t my_idx = 0;
-            float my_w = 0.f;
-            if (lane < wn) {
-                my_idx = cscrow[wb + lane];
-                if (KIND == GNN_AGG_GCN_SYM)
-                    my_w = src_norm[my_idx] * wj;
-                else
-                    my_w = 1.f / static_cast<float>(rowptr[my_idx + 1] - rowptr[my_idx]);
-            }
-            window_accumulate<VEC>(acc, d_a, ka, nbr_off, f, my_idx, my_w, wn, slot, S, active, e0);
+        for (int32_t t = 0; t < len; t += 4) {
+            int32_t i[4];
+            float w[4];
+            float4 v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (t + q < len) i[q] = cscrow[beg + t + q];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (t + q < len) {
+                    i[q] = maybe_scalar<UNI>(i[q]);
+                    v[q] = load_chunk<VEC>(d_a + (static_cast<int64_t>(i[q]) * ka + nbr_off), 0, e0, f);
+                    if (KIND == GNN_AGG_GCN_SYM)
+                        w[q] = src_norm[i[q]] * wj;
+                    else
+                        w[q] = 1.f / static_cast<float>(rowptr[i[q] + 1] - rowptr[i[q]]);
+                }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (t + q < len) fma4(acc, w[q], v[q]);
         }
-        for (int s2 = 1; s2 < S; ++s2) {
-            const float4 o = shfl4(acc, lane + s2 * C);
-            if (slot == 0) {
-                acc.x += o.x;
-                acc.y += o.y;
-                acc.z += o.z;
-                acc.w += o.w;
-            }
-        }
-        if (slot != 0 || !active) continue;
         if (j < n_dst) {
             const float ws = (KIND == GNN_AGG_GCN_SYM) ? wj * wj : 1.f;
             fma4(acc, ws, self);
@@ -233,9 +326,8 @@ __device__ __forceinline__ void agg_bwd_row(int64_t n_dst, const int64_t *__rest
 // alone, four edges in flight, is still at it when the rest of the grid has
 // finished. Such columns are put aside (LongColumns) and summed by the
 // whole workgroup afterwards, a thread per element and kLongAhead edges in
-// flight, the edges in the same sequence (for rows of more than 128 elements,
-// whose wavefronts walk all edges in sequence, the sums are the same bit for
-// bit). At 8,192 targets (fanout 25, f = 256; the longest column has about 180
+// flight, the edges in the same sequence, so the sums are the same bit for bit.
+// At 8,192 targets (fanout 25, f = 256; the longest column has about 180
 // of the 59k edges) the mean's backward took 36 us, now 32, the
 // maximum's 79 us, now 43.
 constexpr int kLong = 16;       // longest column of one wavefront
@@ -244,16 +336,42 @@ struct LongColumns {
     static constexpr int kCap = 64;  // columns past it stay with their wavefronts
     int n;
     int32_t j[kCap];
-    // One wavefront: put column c (uniform) aside; false when there is no room.
-    __device__ __forceinline__ bool add(int64_t c) {
-        int at = 0;
-        if ((threadIdx.x & 63) == 0) {
+    // The lanes of a row (`first` the row's first): put column c aside when
+    // wanted; false where it is not or there is no room.
+    __device__ __forceinline__ bool add(int64_t c, bool want, int first) {
+        int at = kCap;
+        if (want && static_cast<int>(threadIdx.x & 63) == first) {
             at = atomicAdd(&n, 1);
             if (at < kCap) j[at] = static_cast<int32_t>(c);
         }
-        return __builtin_amdgcn_readfirstlane(at) < kCap;
+        return __shfl(at, first, 64) < kCap;
     }
 };
+// Calls row(j, beg, len) in every lane that has a column of its own, for the
+// columns of this workgroup, R per wavefront, and long_row(j, beg, end) in all
+// threads for those put aside.
+template <bool UNI, class Row, class LongRow>
+__device__ __forceinline__ void walk_columns(const gnn_block &b, int64_t blk, int64_t nblk, int C, int R,
+                                             const RowLanes &L, Row &&row, LongRow &&long_row) {
+    __shared__ LongColumns aside;
+    const int64_t n_src = b.counts[1];
+    const int first = L.r * (C > 64 ? 64 : C);
+    if (threadIdx.x == 0) aside.n = 0;
+    __syncthreads();
+    for (int64_t j0 = (blk * kWaves + (threadIdx.x >> 6)) * R; j0 < n_src; j0 += nblk * kWaves * R) {
+        const bool live = L.active && j0 + L.r < n_src;
+        int64_t j = live ? j0 + L.r : j0;
+        if constexpr (UNI) j = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(j));  // (local ids are 32-bit)
+        const int64_t beg = b.cscptr[j], end = b.cscptr[j + 1];
+        const bool put = aside.add(j, live && end - beg > kLong, live ? first : 0);
+        if (live && !put) row(j, beg, maybe_scalar<UNI>(static_cast<int32_t>(end - beg)));
+    }
+    __syncthreads();
+    for (int i = 0; i < min(aside.n, LongColumns::kCap); ++i) {
+        const int64_t j = aside.j[i];
+        long_row(j, b.cscptr[j], b.cscptr[j + 1]);
+    }
+}
 
 template <int KIND, class THB>
 __device__ __forceinline__ void agg_bwd_long(int64_t n_dst, const int64_t *__restrict__ rowptr,
@@ -265,10 +383,10 @@ __device__ __forceinline__ void agg_bwd_long(int64_t n_dst, const int64_t *__res
     const int64_t nbr_off = (KIND == GNN_AGG_SAGE_MEAN) ? f : 0;
     const float wj = (KIND == GNN_AGG_GCN_SYM) ? src_norm[j] : 1.f;
     // a wavefront past the row has nothing to add (e0 is uniform in it)
-    for (int64_t e0 = threadIdx.x - lane; e0 < f; e0 += kThreads) {
-        const int64_t e = min(e0 + lane, f - 1);
-        const float self = d_a[(j < n_dst ? j : 0) * ka + e];
-        const float hb = h_below ? Elem<THB>::load(h_below, j * f + e) : 1.f;
+    for (uint32_t e0 = threadIdx.x - lane; e0 < f; e0 += kThreads) {
+        const uint32_t e = min(e0 + lane, static_cast<uint32_t>(f) - 1);
+        const float self = (d_a + (j < n_dst ? j : 0) * ka)[e];
+        const float hb = h_below ? Elem<THB>::load(h_below + j * f, e) : 1.f;
         float acc = 0.f;
         for (int64_t wb = beg; wb < end; wb += 64) {
             const int wn = static_cast<int>(min<int64_t>(64, end - wb));
@@ -287,7 +405,7 @@ __device__ __forceinline__ void agg_bwd_long(int64_t n_dst, const int64_t *__res
                 for (int u = 0; u < kLongAhead; ++u) {  // (lanes past the window hold row 0 with weight 0)
                     const int64_t i = __builtin_amdgcn_readlane(my_idx, tb + u);
                     w[u] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), tb + u));
-                    v[u] = d_a[i * ka + nbr_off + e];
+                    v[u] = (d_a + i * ka + nbr_off)[e];
                 }
 #pragma unroll
                 for (int u = 0; u < kLongAhead; ++u) acc = fmaf(w[u], tb + u < wn ? v[u] : 0.f, acc);
@@ -295,7 +413,7 @@ __device__ __forceinline__ void agg_bwd_long(int64_t n_dst, const int64_t *__res
         }
         if (j < n_dst) acc = fmaf((KIND == GNN_AGG_GCN_SYM) ? wj * wj : 1.f, self, acc);
         if (!(hb > 0.f)) acc = 0.f;
-        if (e0 + lane < f) d_src[j * f + e] = acc;
+        if (e0 + lane < f) (d_src + j * f)[e] = acc;
     }
 }
 
@@ -304,132 +422,62 @@ __device__ __forceinline__ void agg_bwd_long(int64_t n_dst, const int64_t *__res
 // hold workgroups that read the row count only to exit).
 constexpr int64_t kMaxBlocks = 2048;
 
-// The input layer's forward aggregation straight from an fp32 feature table
-// (the feature loading fused into the aggregation, for tables in device
-// memory): row i's p-th sampled neighbour is the global vertex gids[i k + p]
-// (the sampler's staging of the block, in the block's column order), whose
-// table row is read and rounded to bf16 element by element, exactly as the
-// gather would have stored it in X'.  Same lanes, slots and summation order
-// as agg_fwd_row over X', so the result is bitwise the same.  The GCN
-// self term and weights use X' (its destination rows) and the graph's
-// normalisers of the global ids (src_norm of the block holds the same
-// values).
-template <int KIND, bool VEC>
-__device__ __forceinline__ void agg_fwd_row_table(const int64_t *__restrict__ rowptr,
-                                                  const int64_t *__restrict__ gids, int32_t k,
-                                                  const float *__restrict__ src_norm,
-                                                  const float *__restrict__ gcn_norm, const float *__restrict__ table,
-                                                  int64_t row_stride, const uint16_t *__restrict__ x_self, int64_t f,
-                                                  int C, int S, uint16_t *__restrict__ out, int64_t row) {
-    const int lane = threadIdx.x & 63;
-    const int64_t beg = rowptr[row], end = rowptr[row + 1];
-    const int64_t deg = end - beg;
-    const float wi = (KIND == GNN_AGG_GCN_SYM) ? src_norm[row] : 1.f;
-    const int groups = (C + 63) / 64;
-    const int slot = (S > 1) ? lane / C : 0;
-    for (int g = 0; g < groups; ++g) {
-        const int chunk = (S > 1) ? lane % C : g * 64 + lane;
-        const bool active = (S > 1) ? (slot < S) : (chunk < C);
-        const int64_t e0 = active ? static_cast<int64_t>(chunk) * 4 : 0;
-        const float4 self = (KIND == GNN_AGG_GCN_SYM) ? load_chunk<VEC>(x_self, row * f, e0, f)
-                                                        : make_float4(0.f, 0.f, 0.f, 0.f);
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int64_t wb = beg; wb < end; wb += 64) {
-            const int wn = static_cast<int>(min<int64_t>(64, end - wb));
-            int32_t my_idx = 0;
-            float my_w = 0.f;
-            if (lane < wn) {
-                const int64_t gv = gids[row * k + (wb - beg) + lane];
-                my_idx = static_cast<int32_t>(gv);
-                my_w = (KIND == GNN_AGG_GCN_SYM) ? wi * gcn_norm[gv] : 1.f;
-            }
-            window_accumulate<VEC, float, true>(acc, table, row_stride, 0, f, my_idx, my_w, wn, slot, S, active, e0);
-        }
-        for (int s2 = 1; s2 < S; ++s2) {
-            const float4 o = shfl4(acc, lane + s2 * C);
-            if (slot == 0) {
-                acc.x += o.x;
-                acc.y += o.y;
-                acc.z += o.z;
-                acc.w += o.w;
-            }
-        }
-        if (slot != 0 || !active) continue;
-        if (KIND == GNN_AGG_SAGE_MEAN) {
-            if (deg > 0) {
-                const float d = static_cast<float>(deg);
-                acc.x /= d;
-                acc.y /= d;
-                acc.z /= d;
-                acc.w /= d;
-            }
-        } else {
-            const float ws = wi * wi;
-            fma4(acc, ws, self);
-        }
-        store_chunk<VEC>(out, row * f, e0, f, acc);
-    }
-}
-
 template <int KIND, bool VEC>
 struct FwdTableJob {
     gnn_block b;
-    const int64_t *gids;
-    int32_t k;
-    const float *gcn_norm;
-    const float *table;
-    int64_t row_stride;
+    TableEdges edges;
     const uint16_t *x_self;
     int64_t f;
     int C, S;
     uint16_t *out;
     __device__ void run(int64_t blk, int64_t nblk) const {
         const int64_t n = b.counts[0];
+        const RowLanes L(C, S, 1);
         for (int64_t row = blk * kWaves + (threadIdx.x >> 6); row < n; row += nblk * kWaves)
-            agg_fwd_row_table<KIND, VEC>(b.rowptr, gids, k, b.src_norm, gcn_norm, table, row_stride, x_self, f, C, S,
-                                         out, row);
+            agg_fwd_rows<KIND, 4, VEC>(edges, b.rowptr, b.src_norm, x_self, n, f, C, S, L, out, row);
     }
 };
 
-template <int KIND, class TIn, class TOut, bool VEC>
+template <int KIND, class TIn, class TOut, int E, bool VEC>
 struct FwdJob {
     gnn_block b;
     const TIn *h;
     int64_t f;
-    int C, S;
+    int CL, S, R;
     TOut *out;
+    // the grid's 8 workgroups per CU run at once (with more registers a
+    // quarter of them would run alone afterwards)
+    static constexpr int kWavesPerSimd = E == 8 || VEC ? 8 : 1;
     __device__ void run(int64_t blk, int64_t nblk) const {
         const int64_t n = b.counts[0];
-        for (int64_t row = blk * kWaves + (threadIdx.x >> 6); row < n; row += nblk * kWaves)
-            agg_fwd_row<KIND, TIn, TOut, VEC>(b.rowptr, b.col, b.src_norm, h, f, C, S, out, row);
+        const RowLanes L(CL, S, R);
+        const BlockEdges<TIn> edges{b.col, b.src_norm, h, f};
+        for (int64_t row = (blk * kWaves + (threadIdx.x >> 6)) * R; row < n; row += nblk * kWaves * R)
+            agg_fwd_rows<KIND, E, VEC>(edges, b.rowptr, b.src_norm, h, n, f, CL, S, L, out, row);
     }
 };
 
-template <int KIND, class THB, bool VEC>
+template <int KIND, class THB, bool VEC, bool UNI>
 struct BwdJob {
     gnn_block b;
     const float *d_a;
     int64_t f;
-    int C, S;
+    int C, R;
     const THB *h_below;
     float *d_src;
+    static constexpr int kWavesPerSimd = VEC && UNI ? 8 : 1;  // (as FwdJob's)
     __device__ void run(int64_t blk, int64_t nblk) const {
-        __shared__ LongColumns aside;
-        const int64_t n_dst = b.counts[0], n_src = b.counts[1];
-        if (threadIdx.x == 0) aside.n = 0;
-        __syncthreads();
-        for (int64_t j = blk * kWaves + (threadIdx.x >> 6); j < n_src; j += nblk * kWaves) {
-            const int64_t beg = b.cscptr[j], end = b.cscptr[j + 1];
-            if (end - beg > kLong && aside.add(j)) continue;
-            agg_bwd_row<KIND, THB, VEC>(n_dst, b.rowptr, b.cscrow, b.src_norm, d_a, f, C, S, h_below, d_src, j, beg,
-                                        end);
-        }
-        __syncthreads();
-        for (int i = 0; i < min(aside.n, LongColumns::kCap); ++i) {
-            const int64_t j = aside.j[i];
-            agg_bwd_long<KIND, THB>(n_dst, b.rowptr, b.cscrow, b.src_norm, d_a, f, h_below, d_src, j, b.cscptr[j],
-                                    b.cscptr[j + 1]);
-        }
+        const int64_t n_dst = b.counts[0];
+        const RowLanes L(C, 1, R);
+        walk_columns<UNI>(
+            b, blk, nblk, C, R, L,
+            [&](int64_t j, int64_t beg, int32_t len) {
+                agg_bwd_rows<KIND, THB, VEC, UNI>(n_dst, b.rowptr, b.cscrow, b.src_norm, d_a, f, C, L, h_below, d_src, j,
+                                                  beg, len);
+            },
+            [&](int64_t j, int64_t beg, int64_t end) {
+                agg_bwd_long<KIND, THB>(n_dst, b.rowptr, b.cscrow, b.src_norm, d_a, f, h_below, d_src, j, beg, end);
+            });
     }
 };
 
@@ -551,90 +599,74 @@ __device__ __forceinline__ void agg_fwd_row_max(const int64_t *__restrict__ rowp
 // of j's column (the columns are in ascending row order), and only the
 // first of them counts: the maximum passes its gradient once.  The
 // neighbour rows of d_a are read only for elements that j won.
-template <class THB, bool VEC>
-__device__ __forceinline__ void agg_bwd_row_max(int64_t n_dst, const int32_t *__restrict__ cscrow,
-                                                const int32_t *__restrict__ argmax, const float *__restrict__ d_a,
-                                                int64_t f, int C, int S, const THB *__restrict__ h_below,
-                                                float *__restrict__ d_src, int64_t j, int64_t beg, int64_t end) {
-    const int lane = threadIdx.x & 63;
+template <class THB, bool VEC, bool UNI>
+__device__ __forceinline__ void agg_bwd_rows_max(int64_t n_dst, const int32_t *__restrict__ cscrow,
+                                                 const int32_t *__restrict__ argmax, const float *__restrict__ d_a,
+                                                 int64_t f, int C, const RowLanes &L,
+                                                 const THB *__restrict__ h_below, float *__restrict__ d_src, int64_t j,
+                                                 int64_t beg, int32_t len) {
     const int64_t ka = 2 * f;
     const int32_t jj = static_cast<int32_t>(j);
-    const int groups = (C + 63) / 64;
-    const int slot = (S > 1) ? lane / C : 0;
-    for (int g = 0; g < groups; ++g) {
-        const int chunk = (S > 1) ? lane % C : g * 64 + lane;
-        const bool active = (S > 1) ? (slot < S) : (chunk < C);
-        const int64_t e0 = active ? static_cast<int64_t>(chunk) * 4 : 0;
-        const float4 self = load_chunk<VEC>(d_a, (j < n_dst ? j : 0) * ka, e0, f);
-        const bool mask = h_below != nullptr;
-        const float4 hb = load_chunk<VEC>(mask ? h_below : reinterpret_cast<const THB *>(d_a), mask ? j * f : 0, e0, f);
-        float acc[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int64_t wb = beg; wb < end; wb += 64) {
-            const int wn = static_cast<int>(min<int64_t>(64, end - wb));
-            int32_t my_idx = 0;
-            int my_first = 0;
-            if (lane < wn) {
-                my_idx = cscrow[wb + lane];
-                my_first = (wb + lane == beg) || (cscrow[wb + lane - 1] != my_idx);
-            }
-            for (int tb = 0; tb < wn; tb += 4 * S) {
-                int32_t i[4];
-                bool ok[4];
+    const bool mask = h_below != nullptr;
+    for (int chunk = L.chunk; chunk < C; chunk += 64) {
+        const uint32_t e0 = static_cast<uint32_t>(chunk) * 4;
+        float4 self, hb;
+        if (j < n_dst) self = load_chunk<VEC>(d_a + j * ka, 0, e0, f);
+        if (mask) hb = load_chunk<VEC>(h_below + j * f, 0, e0, f);
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        int32_t before = -1;  // the last entry's row
+        for (int32_t t = 0; t < len; t += 4) {
+            int32_t i[4];
+            int4 a[4];
+            float4 v[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    // both shuffles run in every lane: a lane left out would
-                    // read as zero to the lanes that take its value
-                    const int t = tb + u * S + slot;
-                    i[u] = __shfl(my_idx, t & 63, 64);
-                    const int first = __shfl(my_first, t & 63, 64);
-                    ok[u] = active && (t < wn) && first;
+            for (int q = 0; q < 4; ++q)
+                if (t + q < len) i[q] = cscrow[beg + t + q];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (t + q < len) {
+                    i[q] = maybe_scalar<UNI>(i[q]);
+                    a[q] = load_arg4<VEC>(argmax + static_cast<int64_t>(i[q]) * f, 0, e0, f, -1);
                 }
-                int4 a[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) a[u] = load_arg4<VEC>(argmax, static_cast<int64_t>(i[u]) * f, e0, f, -1);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const bool w[4] = {ok[u] && a[u].x == jj, ok[u] && a[u].y == jj, ok[u] && a[u].z == jj,
-                                       ok[u] && a[u].w == jj};
-                    if (w[0] || w[1] || w[2] || w[3]) {
-                        const float4 v = load_chunk<VEC>(d_a, static_cast<int64_t>(i[u]) * ka + f, e0, f);
-                        acc[0] += w[0] ? v.x : 0.f;
-                        acc[1] += w[1] ? v.y : 0.f;
-                        acc[2] += w[2] ? v.z : 0.f;
-                        acc[3] += w[3] ? v.w : 0.f;
-                    }
-                }
-            }
-        }
-        for (int s2 = 1; s2 < S; ++s2) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const float o = __shfl(acc[q], lane + s2 * C, 64);
-                if (slot == 0) acc[q] += o;
+                if (t + q >= len) continue;
+                const bool first = i[q] != before;
+                before = i[q];
+                a[q].x = first && a[q].x == jj;
+                a[q].y = first && a[q].y == jj;
+                a[q].z = first && a[q].z == jj;
+                a[q].w = first && a[q].w == jj;
+                if (a[q].x | a[q].y | a[q].z | a[q].w)
+                    v[q] = load_chunk<VEC>(d_a + (static_cast<int64_t>(i[q]) * ka + f), 0, e0, f);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (t + q >= len || !(a[q].x | a[q].y | a[q].z | a[q].w)) continue;
+                acc.x += a[q].x ? v[q].x : 0.f;
+                acc.y += a[q].y ? v[q].y : 0.f;
+                acc.z += a[q].z ? v[q].z : 0.f;
+                acc.w += a[q].w ? v[q].w : 0.f;
             }
         }
-        if (slot != 0 || !active) continue;
-        float4 r = make_float4(acc[0], acc[1], acc[2], acc[3]);
         if (j < n_dst) {
-            r.x += self.x;
-            r.y += self.y;
-            r.z += self.z;
-            r.w += self.w;
+            acc.x += self.x;
+            acc.y += self.y;
+            acc.z += self.z;
+            acc.w += self.w;
         }
         if (mask) {
-            if (!(hb.x > 0.f)) r.x = 0.f;
-            if (!(hb.y > 0.f)) r.y = 0.f;
-            if (!(hb.z > 0.f)) r.z = 0.f;
-            if (!(hb.w > 0.f)) r.w = 0.f;
+            if (!(hb.x > 0.f)) acc.x = 0.f;
+            if (!(hb.y > 0.f)) acc.y = 0.f;
+            if (!(hb.z > 0.f)) acc.z = 0.f;
+            if (!(hb.w > 0.f)) acc.w = 0.f;
         }
-        store_chunk<VEC>(d_src, j * f, e0, f, r);
+        store_chunk<VEC>(d_src, j * f, e0, f, acc);
     }
 }
 
 // A long column of the maximum's backward, by the whole workgroup
-// (agg_bwd_long's split and order). Elements that j did not win read the
-// self part's element instead of their row's (a line that is at hand), so that
-// a batch's loads need no branches.
+// (agg_bwd_long's split and order).
 template <class THB>
 __device__ __forceinline__ void agg_bwd_long_max(int64_t n_dst, const int32_t *__restrict__ cscrow,
                                                  const int32_t *__restrict__ argmax, const float *__restrict__ d_a,
@@ -643,10 +675,10 @@ __device__ __forceinline__ void agg_bwd_long_max(int64_t n_dst, const int32_t *_
     const int lane = threadIdx.x & 63;
     const int64_t ka = 2 * f;
     const int32_t jj = static_cast<int32_t>(j);
-    for (int64_t e0 = threadIdx.x - lane; e0 < f; e0 += kThreads) {
-        const int64_t e = min(e0 + lane, f - 1), self_at = (j < n_dst ? j : 0) * ka + e;
-        const float self = d_a[self_at];
-        const float hb = h_below ? Elem<THB>::load(h_below, j * f + e) : 1.f;
+    for (uint32_t e0 = threadIdx.x - lane; e0 < f; e0 += kThreads) {
+        const uint32_t e = min(e0 + lane, static_cast<uint32_t>(f) - 1);
+        const float self = (d_a + (j < n_dst ? j : 0) * ka)[e];
+        const float hb = h_below ? Elem<THB>::load(h_below + j * f, e) : 1.f;
         float acc = 0.f;
         for (int64_t wb = beg; wb < end; wb += 64) {
             const int wn = static_cast<int>(min<int64_t>(64, end - wb));
@@ -662,14 +694,13 @@ __device__ __forceinline__ void agg_bwd_long_max(int64_t n_dst, const int32_t *_
 #pragma unroll
                 for (int u = 0; u < kLongAhead; ++u) {
                     const int64_t i = __builtin_amdgcn_readlane(my_idx, tb + u);
-                    a[u] = argmax[(i < 0 ? 0 : i) * f + e];
+                    a[u] = (argmax + (i < 0 ? 0 : i) * f)[e];
                 }
 #pragma unroll
                 for (int u = 0; u < kLongAhead; ++u) {
                     const int64_t i = __builtin_amdgcn_readlane(my_idx, tb + u);
-                    const bool won = i >= 0 && a[u] == jj;
-                    const float x = d_a[won ? i * ka + f + e : self_at];
-                    v[u] = won ? x : 0.f;
+                    v[u] = 0.f;
+                    if (i >= 0 && a[u] == jj) v[u] = (d_a + i * ka + f)[e];
                 }
 #pragma unroll
                 for (int u = 0; u < kLongAhead; ++u) acc += v[u];
@@ -677,7 +708,7 @@ __device__ __forceinline__ void agg_bwd_long_max(int64_t n_dst, const int32_t *_
         }
         if (j < n_dst) acc += self;
         if (!(hb > 0.f)) acc = 0.f;
-        if (e0 + lane < f) d_src[j * f + e] = acc;
+        if (e0 + lane < f) (d_src + j * f)[e] = acc;
     }
 }
 
@@ -696,30 +727,27 @@ struct FwdMaxJob {
     }
 };
 
-template <class THB, bool VEC>
+template <class THB, bool VEC, bool UNI>
 struct BwdMaxJob {
     gnn_block b;
     const int32_t *argmax;
     const float *d_a;
     int64_t f;
-    int C, S;
+    int C, R;
     const THB *h_below;
     float *d_src;
+    static constexpr int kWavesPerSimd = VEC && UNI ? 8 : 1;  // (as FwdJob's)
     __device__ void run(int64_t blk, int64_t nblk) const {
-        __shared__ LongColumns aside;
-        const int64_t n_dst = b.counts[0], n_src = b.counts[1];
-        if (threadIdx.x == 0) aside.n = 0;
-        __syncthreads();
-        for (int64_t j = blk * kWaves + (threadIdx.x >> 6); j < n_src; j += nblk * kWaves) {
-            const int64_t beg = b.cscptr[j], end = b.cscptr[j + 1];
-            if (end - beg > kLong && aside.add(j)) continue;
-            agg_bwd_row_max<THB, VEC>(n_dst, b.cscrow, argmax, d_a, f, C, S, h_below, d_src, j, beg, end);
-        }
-        __syncthreads();
-        for (int i = 0; i < min(aside.n, LongColumns::kCap); ++i) {
-            const int64_t j = aside.j[i];
-            agg_bwd_long_max<THB>(n_dst, b.cscrow, argmax, d_a, f, h_below, d_src, j, b.cscptr[j], b.cscptr[j + 1]);
-        }
+        const int64_t n_dst = b.counts[0];
+        const RowLanes L(C, 1, R);
+        walk_columns<UNI>(
+            b, blk, nblk, C, R, L,
+            [&](int64_t j, int64_t beg, int32_t len) {
+                agg_bwd_rows_max<THB, VEC, UNI>(n_dst, b.cscrow, argmax, d_a, f, C, L, h_below, d_src, j, beg, len);
+            },
+            [&](int64_t j, int64_t beg, int64_t end) {
+                agg_bwd_long_max<THB>(n_dst, b.cscrow, argmax, d_a, f, h_below, d_src, j, beg, end);
+            });
     }
 };
 
@@ -728,6 +756,9 @@ inline void split_row(int64_t f, int *C, int *S) {
     *C = static_cast<int>(c);
     *S = (c <= 32) ? static_cast<int>(64 / c) : 1;
 }
+
+// Rows per wavefront when each takes ceil(f / 4) lanes.
+inline int rows_per_wave(int64_t f) { return static_cast<int>(std::max<int64_t>(1, 64 / ceil_div(f, 4))); }
 
 inline unsigned row_grid(int64_t rows) {
     return static_cast<unsigned>(std::min<int64_t>(ceil_div(rows > 0 ? rows : 1, kWaves), kMaxBlocks));
@@ -744,8 +775,9 @@ void with_fwd_table_job(const gnn_block *b, int kind, const int64_t *gids, int32
                      aligned(out, 8);
     auto go = [&](auto kind_tag) {
         constexpr int KIND = decltype(kind_tag)::value;
-        if (vec) fn(FwdTableJob<KIND, true>{*b, gids, k, gcn_norm, table, row_stride, x_self, f, C, S, out});
-        else fn(FwdTableJob<KIND, false>{*b, gids, k, gcn_norm, table, row_stride, x_self, f, C, S, out});
+        const TableEdges edges{gids, k, gcn_norm, table, row_stride};
+        if (vec) fn(FwdTableJob<KIND, true>{*b, edges, x_self, f, C, S, out});
+        else fn(FwdTableJob<KIND, false>{*b, edges, x_self, f, C, S, out});
     };
     if (kind == GNN_AGG_SAGE_MEAN) go(std::integral_constant<int, GNN_AGG_SAGE_MEAN>{});
     else go(std::integral_constant<int, GNN_AGG_GCN_SYM>{});
@@ -763,8 +795,15 @@ bool with_fwd_job(const gnn_block *b, int kind, const void *h, int hdt, int64_t 
         using TO = typename decltype(to_tag)::type;
         const TI *hp = static_cast<const TI *>(h);
         TO *op = static_cast<TO *>(out);
-        if (vec) fn(FwdJob<KIND, TI, TO, true>{*b, hp, f, C, S, op});
-        else fn(FwdJob<KIND, TI, TO, false>{*b, hp, f, C, S, op});
+        if constexpr (sizeof(TI) == 2) {
+            // eight elements per lane: even rows of at least eight, dword aligned
+            if (f % 2 == 0 && f >= 8 && aligned(h, 4) && aligned(out, 4)) {
+                const int CL = static_cast<int>(ceil_div(f, 8)), R = std::max(1, 64 / (S * CL));
+                return fn(FwdJob<KIND, TI, TO, 8, false>{*b, hp, f, CL, S, R, op});
+            }
+        }
+        if (vec) fn(FwdJob<KIND, TI, TO, 4, true>{*b, hp, f, C, S, 1, op});
+        else fn(FwdJob<KIND, TI, TO, 4, false>{*b, hp, f, C, S, 1, op});
     };
     auto by_types = [&](auto kind_tag) {
         if (hdt == GNN_F32 && odt == GNN_F32) by_kind(kind_tag, Tag<float>{}, Tag<float>{});
@@ -782,16 +821,20 @@ bool with_fwd_job(const gnn_block *b, int kind, const void *h, int hdt, int64_t 
 template <class F>
 void with_bwd_job(const gnn_block *b, int kind, const float *d_a, int64_t f, const void *h_below, int hbdt,
                   float *d_src, F &&fn) {
-    int C, S;
-    split_row(f, &C, &S);
+    const int C = static_cast<int>(ceil_div(f, 4)), R = rows_per_wave(f);
     const bool vec = (f % 4 == 0) && aligned(d_a, 16) && aligned(d_src, 16) &&
                      (!h_below || aligned(h_below, 4 * dtype_size(hbdt)));
     auto by_type = [&](auto kind_tag, auto hb_tag) {
         constexpr int KIND = decltype(kind_tag)::value;
         using THB = typename decltype(hb_tag)::type;
         const THB *hb = static_cast<const THB *>(h_below);
-        if (vec) fn(BwdJob<KIND, THB, true>{*b, d_a, f, C, S, hb, d_src});
-        else fn(BwdJob<KIND, THB, false>{*b, d_a, f, C, S, hb, d_src});
+        auto by_rows = [&](auto vec_tag) {
+            constexpr bool V = decltype(vec_tag)::value;
+            if (R == 1) fn(BwdJob<KIND, THB, V, true>{*b, d_a, f, C, R, hb, d_src});
+            else fn(BwdJob<KIND, THB, V, false>{*b, d_a, f, C, R, hb, d_src});
+        };
+        if (vec) by_rows(std::true_type{});
+        else by_rows(std::false_type{});
     };
     auto by_kind = [&](auto kind_tag) {
         if (!h_below || hbdt == GNN_F32) by_type(kind_tag, Tag<float>{});
@@ -838,15 +881,19 @@ bool with_fwd_kind_job(const gnn_block *b, int kind, const void *h, int hdt, int
 template <class F>
 void with_bwd_max_job(const gnn_block *b, const int32_t *argmax, const float *d_a, int64_t f, const void *h_below,
                       int hbdt, float *d_src, F &&fn) {
-    int C, S;
-    split_row(f, &C, &S);
+    const int C = static_cast<int>(ceil_div(f, 4)), R = rows_per_wave(f);
     const bool vec = (f % 4 == 0) && aligned(d_a, 16) && aligned(d_src, 16) && aligned(argmax, 16) &&
                      (!h_below || aligned(h_below, 4 * dtype_size(hbdt)));
     auto go = [&](auto hb_tag) {
         using THB = typename decltype(hb_tag)::type;
         const THB *hb = static_cast<const THB *>(h_below);
-        if (vec) fn(BwdMaxJob<THB, true>{*b, argmax, d_a, f, C, S, hb, d_src});
-        else fn(BwdMaxJob<THB, false>{*b, argmax, d_a, f, C, S, hb, d_src});
+        auto by_rows = [&](auto vec_tag) {
+            constexpr bool V = decltype(vec_tag)::value;
+            if (R == 1) fn(BwdMaxJob<THB, V, true>{*b, argmax, d_a, f, C, R, hb, d_src});
+            else fn(BwdMaxJob<THB, V, false>{*b, argmax, d_a, f, C, R, hb, d_src});
+        };
+        if (vec) by_rows(std::true_type{});
+        else by_rows(std::false_type{});
     };
     if (!h_below || hbdt == GNN_F32) go(Tag<float>{});
     else go(Tag<uint16_t>{});

@@ -13,8 +13,13 @@
 
 namespace gnn {
 
+// A job may name the wavefronts per SIMD that its registers are to leave room
+// for (kWavesPerSimd); 1 leaves the choice to the compiler.
+template <class J> constexpr auto job_waves(int) -> decltype(J::kWavesPerSimd) { return J::kWavesPerSimd; }
+template <class J> constexpr int job_waves(long) { return 1; }
+
 template <class J>
-__global__ void __launch_bounds__(256) job_kernel(J j) {
+__global__ void __launch_bounds__(256, job_waves<J>(0)) job_kernel(J j) {
     j.run(blockIdx.x, gridDim.x);
 }
 

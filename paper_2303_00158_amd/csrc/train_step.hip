@@ -421,9 +421,9 @@ float *bwd_region(const gnn_model *m, const gnn_step_layout &o, char *comp, int 
 // Both layers' partials are live in launch 2, so each has its own region.
 struct TwoBwd {
     TwoBwdPlan q;  // both layers' dW (q.pull: layer 2's aggregation backward folded into layer 1's)
-    agg::BwdJob<GNN_AGG_SAGE_MEAN, uint16_t, true> sage_bwd;  // else G^1 through memory
-    agg::BwdJob<GNN_AGG_GCN_SYM, uint16_t, true> gcn_bwd;
-    agg::BwdMaxJob<uint16_t, true> max_bwd;  // (the max aggregator's, through its argmax table)
+    agg::BwdJob<GNN_AGG_SAGE_MEAN, uint16_t, true, false> sage_bwd;  // else G^1 through memory
+    agg::BwdJob<GNN_AGG_GCN_SYM, uint16_t, true, false> gcn_bwd;
+    agg::BwdMaxJob<uint16_t, true, false> max_bwd;  // (the max aggregator's, through its argmax table)
     bool ok;
 };
 
@@ -441,11 +441,10 @@ TwoBwd two_layer_bwd_plan(const gnn_model *m, const gnn_block *blk, const void *
                        bwd_region(m, o, comp, 1), m->w[0], m->b[0], m->wt[0], m->w[1], m->dw[1], m->db[1],
                        bwd_region(m, o, comp, 2), m->w[1], m->b[1], m->wt[1], lr);
     t.q.a1.g = g1;  // the unfused path's G^1
-    int C, S;
-    agg::split_row(f1, &C, &S);
-    t.sage_bwd = {b2, d_a2, f1, C, S, h1, g1};
-    t.gcn_bwd = {b2, d_a2, f1, C, S, h1, g1};
-    t.max_bwd = {b2, arg2, d_a2, f1, C, S, h1, g1};
+    const int C = static_cast<int>(ceil_div(f1, 4)), R = agg::rows_per_wave(f1);
+    t.sage_bwd = {b2, d_a2, f1, C, R, h1, g1};
+    t.gcn_bwd = {b2, d_a2, f1, C, R, h1, g1};
+    t.max_bwd = {b2, arg2, d_a2, f1, C, R, h1, g1};
     const TwoBwdPlan &q = t.q;
     t.ok = m->precision == GNN_BF16 && q.gemm_ok && f1 % 4 == 0 && aligned(d_a2, 16) && aligned(g1, 16) &&
            aligned(h1, 8) && aligned(arg2, 16) &&

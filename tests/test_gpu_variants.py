@@ -194,3 +194,37 @@ def test_aggregate_bwd_long_columns(kind, f):
         gnn.aggregate_bwd(b, gk, d_a_d, f, d_src, h_d)
     # fp32 sums of up to 900 terms: within 900 2^-24 of the terms' magnitude sum
     assert relerr(d_src.cpu().numpy(), want) <= 1e-5
+
+
+# Forward sums: bf16 rows of an even number of elements, at least eight, on a
+# 4-byte boundary take eight elements per lane and up to two rows per
+# wavefront; others four. The slots' order is that of the tile-deduplicated
+# aggregation for all of them.
+@pytest.mark.parametrize("f", [1, 2, 6, 7, 8, 10, 12, 16, 50, 98, 100, 101, 102, 128, 130, 256, 258, 514, 600])
+@pytest.mark.parametrize("shift", [0, 1, 2])
+def test_aggregate_fwd_lanes(f, shift):
+    from tests.test_gpu_parity import from_np_act, to_np_act, relerr, upload_block
+    rng = np.random.default_rng(f)
+    n = 300
+    rows = [rng.choice(n, size=int(d), replace=True) for d in rng.choice([0, 1, 2, 3, 8, 9, 17, 64, 65, 130], size=n)]
+    rowptr, col = csr(rows)
+    blk = oracle.build_block(rowptr, col, rng.permutation(n)[:211].astype(np.int64), 200, 1, 1, 1)
+    norm = rng.uniform(0.1, 1, size=blk.n_src).astype(np.float32)
+    b = upload_block(blk, norm)
+    for dt in (torch.bfloat16, torch.float32):
+        base = torch.zeros(blk.n_src * f + 8, dtype=dt, device=DEV)
+        h = base[shift:shift + blk.n_src * f].view(blk.n_src, f)  # rows on any element boundary
+        h.copy_(torch.from_numpy(rng.standard_normal((blk.n_src, f)).astype(np.float32)))
+        for okind, kind in ((oracle.SAGE, gnn.GNN_AGG_SAGE_MEAN), (oracle.GCN, gnn.GNN_AGG_GCN_SYM)):
+            for odt in (torch.bfloat16, torch.float32):
+                obase = torch.full((blk.n_dst * f + 8,), 7.0, dtype=odt, device=DEV)
+                out = obase[shift:shift + blk.n_dst * f].view(blk.n_dst, f)
+                gnn.aggregate_fwd(b, kind, h, out)
+                dedup = torch.empty((blk.n_dst, f), dtype=odt, device=DEV)
+                gnn.aggregate_fwd_dedup(b, kind, h.contiguous(), dedup)
+                want = oracle.aggregate_fwd(okind, blk, norm, to_np_act(h), oracle.F64)
+                # fp32 sums of up to 200 terms; a bf16 result rounds by at most 2^-8 relative
+                assert relerr(out.float().cpu().numpy(), want) <= (2.0 ** -8 if odt == torch.bfloat16 else 1e-5)
+                assert torch.equal(out, dedup)
+                rest = torch.cat([obase[:shift], obase[shift + blk.n_dst * f:]])
+                assert bool((rest == 7.0).all())  # nothing beside the rows is written
