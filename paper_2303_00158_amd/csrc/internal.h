@@ -67,13 +67,12 @@ constexpr int64_t kMaxGrid = (1ll << 31) - 1;
 // ---------------------------------------------------------------------------
 // device helpers
 // ---------------------------------------------------------------------------
-// fp32 -> bf16, round to nearest even; NaNs stay NaN (quiet bit set).
-// Written without branches so it vectorises inside unrolled loops.
+// fp32 -> bf16, round to nearest even; NaNs stay NaN (quiet bit set): the
+// gfx950 conversion, which gives the bits of the integer form
+// (u + 0x7fff + (u >> 16 & 1)) >> 16, or (u >> 16) | 0x40 for NaNs, for all
+// 2^32 inputs, in one instruction for two values instead of some ten.
 __device__ __forceinline__ uint16_t f32_to_bf16(float x) {
-    const uint32_t u = __float_as_uint(x);
-    const uint32_t rounded = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-    const uint32_t quiet = (u >> 16) | 0x40u;
-    return static_cast<uint16_t>(((u & 0x7fffffffu) > 0x7f800000u) ? quiet : rounded);
+    return __builtin_bit_cast(uint16_t, static_cast<__bf16>(x));
 }
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float(static_cast<uint32_t>(h) << 16); }
 __device__ __forceinline__ float f16_to_f32(uint16_t h) {
