@@ -23,15 +23,42 @@ struct Args {
     int64_t cap, dim;
     void *out;
 };
+// An output larger than the L2s is not at hand for whoever reads it next: rows
+// and output then bypass them (non-temporal; the jobs' STREAM), which leaves
+// the L2s to rows that repeat. 334,699 rows of 100 fp32 values to bf16: 47.6 us
+// with cached accesses, 44.1 us so; the training step's small X', read by the
+// next launches, loses by it (553 to 556 us for 8 steps).
+constexpr int64_t kStreamBytes = 32 << 20;
 
 template <class T> struct Raw4;
 template <> struct Raw4<float> { using type = uint4; };
 template <> struct Raw4<uint16_t> { using type = uint2; };
 
-// Widening / narrowing of a 4-element chunk.
-__device__ __forceinline__ float4 load4_table(const float *p) { return *reinterpret_cast<const float4 *>(p); }
-__device__ __forceinline__ float4 load4_f16(const uint16_t *p) {
-    const uint2 v = *reinterpret_cast<const uint2 *>(p);
+// A 4-element chunk of either width, through the caches or past them.
+template <bool STREAM, class V> __device__ __forceinline__ V load_raw(const void *p) {
+    typedef uint32_t words __attribute__((ext_vector_type(sizeof(V) / 4)));
+    const words *w = static_cast<const words *>(p);
+    if constexpr (STREAM) return __builtin_bit_cast(V, __builtin_nontemporal_load(w));
+    return __builtin_bit_cast(V, *w);
+}
+template <bool STREAM, class V> __device__ __forceinline__ void store_raw(void *p, const V &v) {
+    typedef uint32_t words __attribute__((ext_vector_type(sizeof(V) / 4)));
+    words *w = static_cast<words *>(p);
+    if constexpr (STREAM)
+        __builtin_nontemporal_store(__builtin_bit_cast(words, v), w);
+    else
+        *w = __builtin_bit_cast(words, v);
+}
+
+// Four values in the output's type.
+template <class T> __device__ __forceinline__ typename Raw4<T>::type narrow4(const float4 &v) {
+    if constexpr (sizeof(T) == 4)
+        return __builtin_bit_cast(uint4, v);
+    else
+        return make_uint2(static_cast<uint32_t>(f32_to_bf16(v.x)) | (static_cast<uint32_t>(f32_to_bf16(v.y)) << 16),
+                          static_cast<uint32_t>(f32_to_bf16(v.z)) | (static_cast<uint32_t>(f32_to_bf16(v.w)) << 16));
+}
+__device__ __forceinline__ float4 widen_f16(const uint2 &v) {
     return make_float4(f16_to_f32(static_cast<uint16_t>(v.x & 0xffffu)), f16_to_f32(static_cast<uint16_t>(v.x >> 16)),
                        f16_to_f32(static_cast<uint16_t>(v.y & 0xffffu)), f16_to_f32(static_cast<uint16_t>(v.y >> 16)));
 }
@@ -100,7 +127,7 @@ __device__ __forceinline__ void gather_rows(const Args &a, const RowSlots &rs, i
 }
 
 // Same element type on both sides: bit copy of 4-element chunks.
-template <class T>
+template <class T, bool STREAM>
 struct Copy4 {
     Args a;
     RowSlots rs;
@@ -109,12 +136,12 @@ struct Copy4 {
         const T *__restrict__ table = static_cast<const T *>(a.table);
         T *__restrict__ out = static_cast<T *>(a.out);
         gather_rows(
-            a, rs, blk, nblk, [&](int64_t off) { return *reinterpret_cast<const R *>(table + off); },
-            [&](int64_t off, R v) { *reinterpret_cast<R *>(out + off) = v; });
+            a, rs, blk, nblk, [&](int64_t off) { return load_raw<STREAM, R>(table + off); },
+            [&](int64_t off, R v) { store_raw<STREAM>(out + off, v); });
     }
 };
 
-template <bool SRC_F16, class TOut>
+template <bool SRC_F16, class TOut, bool STREAM>
 struct Convert4 {
     Args a;
     RowSlots rs;
@@ -123,19 +150,13 @@ struct Convert4 {
         if constexpr (SRC_F16) {
             const uint16_t *__restrict__ table = static_cast<const uint16_t *>(a.table);
             gather_rows(
-                a, rs, blk, nblk, [&](int64_t off) { return *reinterpret_cast<const uint2 *>(table + off); },
-                [&](int64_t off, uint2 v) {
-                    store4(out, off,
-                           make_float4(f16_to_f32(static_cast<uint16_t>(v.x & 0xffffu)),
-                                       f16_to_f32(static_cast<uint16_t>(v.x >> 16)),
-                                       f16_to_f32(static_cast<uint16_t>(v.y & 0xffffu)),
-                                       f16_to_f32(static_cast<uint16_t>(v.y >> 16))));
-                });
+                a, rs, blk, nblk, [&](int64_t off) { return load_raw<STREAM, uint2>(table + off); },
+                [&](int64_t off, uint2 v) { store_raw<STREAM>(out + off, narrow4<TOut>(widen_f16(v))); });
         } else {
             const float *__restrict__ table = static_cast<const float *>(a.table);
             gather_rows(
-                a, rs, blk, nblk, [&](int64_t off) { return load4_table(table + off); },
-                [&](int64_t off, float4 v) { store4(out, off, v); });
+                a, rs, blk, nblk, [&](int64_t off) { return load_raw<STREAM, float4>(table + off); },
+                [&](int64_t off, float4 v) { store_raw<STREAM>(out + off, narrow4<TOut>(v)); });
         }
     }
 };
@@ -184,7 +205,8 @@ struct Scalar {
 // the GPU.
 constexpr int64_t kHostGrid = 256;
 
-inline unsigned grid_for(int64_t cap, int64_t dim, bool vec, bool host) {
+// counted: the row count is on the device.
+inline unsigned grid_for(int64_t cap, int64_t dim, bool vec, bool host, bool counted) {
     int64_t b;
     if (vec) {
         const RowSlots rs = RowSlots::of(dim);
@@ -192,10 +214,14 @@ inline unsigned grid_for(int64_t cap, int64_t dim, bool vec, bool host) {
     } else {
         b = ceil_div(cap * dim > 0 ? cap * dim : 1, kThreads);
     }
-    // rows are strided over the grid: 2048 workgroups cover the row counts
-    // of the workloads here in one or two rounds without dispatching
-    // workgroups that would only read the row count and exit
-    if (b > 2048) b = 2048;
+    // Rows are strided over the grid. Where the row count is on the device, 2048
+    // workgroups cover the row counts of the workloads here in one or two
+    // rounds without dispatching workgroups that would only read it and
+    // exit. A count known here gets a workgroup for every few rows, so that no
+    // last round is nearly empty (334,699 rows: 5.1 rounds of 2048 workgroups
+    // took 50.3 us, 10,460 workgroups 47.6).
+    const int64_t most = counted ? 2048 : 1 << 20;
+    if (b > most) b = most;
     if (host && b > kHostGrid) b = kHostGrid;
     return static_cast<unsigned>(b);
 }
@@ -206,16 +232,16 @@ inline bool vec_ok(const Args &a, int tdt, int odt) {
 }
 
 // Calls f(job) with the job of the variant serving tdt -> odt; returns false
-// when the pair is not supported.
-template <class F>
+// when the pair is not supported.  STREAM applies to the vector variants.
+template <bool STREAM = false, class F>
 bool with_job(const Args &a, int tdt, int odt, F &&f) {
     if (vec_ok(a, tdt, odt)) {
         const RowSlots rs = RowSlots::of(a.dim);
-        if (tdt == odt && tdt == GNN_F32) return f(Copy4<float>{a, rs}), true;
-        if (tdt == odt) return f(Copy4<uint16_t>{a, rs}), true;
-        if (tdt == GNN_F32 && odt == GNN_BF16) return f(Convert4<false, uint16_t>{a, rs}), true;
-        if (tdt == GNN_F16 && odt == GNN_BF16) return f(Convert4<true, uint16_t>{a, rs}), true;
-        if (tdt == GNN_F16 && odt == GNN_F32) return f(Convert4<true, float>{a, rs}), true;
+        if (tdt == odt && tdt == GNN_F32) return f(Copy4<float, STREAM>{a, rs}), true;
+        if (tdt == odt) return f(Copy4<uint16_t, STREAM>{a, rs}), true;
+        if (tdt == GNN_F32 && odt == GNN_BF16) return f(Convert4<false, uint16_t, STREAM>{a, rs}), true;
+        if (tdt == GNN_F16 && odt == GNN_BF16) return f(Convert4<true, uint16_t, STREAM>{a, rs}), true;
+        if (tdt == GNN_F16 && odt == GNN_F32) return f(Convert4<true, float, STREAM>{a, rs}), true;
         return false;
     }
     if (tdt == GNN_F32 && odt == GNN_F32) return f(Scalar<GNN_F32, GNN_F32>{a}), true;

@@ -209,7 +209,7 @@ gnn_status run_prepare(const gnn_model *m, const gnn_graph *g, const float *gcn_
     // (counts[0]) when the aggregation reads the table itself
     const gath::Args ga{table, row_stride, b0.src_ids, b0.counts + (fuse ? 0 : 1), fuse ? b0.cap_dst : b0.cap_src,
                         m->dims[0], prep + o.x0};
-    const unsigned ggrid = gath::grid_for(ga.cap, m->dims[0], gath::vec_ok(ga, tdt, act), host_table);
+    const unsigned ggrid = gath::grid_for(ga.cap, m->dims[0], gath::vec_ok(ga, tdt, act), host_table, true);
     gnn_status st = GNN_OK;
     const bool ok = gath::with_job(ga, tdt, act, [&](auto job) {
         st = launch_jobs(s, "hop_relabel+gather+csc_place",
@@ -335,7 +335,7 @@ gnn_status run_prepare_group(const gnn_model *m, const gnn_graph *g, const float
     // A host table's rows come over the host link, which a few hundred
     // workgroups in total already saturate: the copies share that budget, so
     // the rest of the GPU stays free for the compute stage running beside.
-    unsigned ggrid = gath::grid_for(ga[0].cap, m->dims[0], gath::vec_ok(ga[0], tdt, act), host_table);
+    unsigned ggrid = gath::grid_for(ga[0].cap, m->dims[0], gath::vec_ok(ga[0], tdt, act), host_table, true);
     if (host_table) ggrid = std::max(1u, std::min(ggrid, static_cast<unsigned>(kHostGroupGrid / G)));
     bool same = true;
     const bool ok = gath::with_job(ga[0], tdt, act, [&](auto job) {

@@ -228,3 +228,23 @@ def test_aggregate_fwd_lanes(f, shift):
                 assert torch.equal(out, dedup)
                 rest = torch.cat([obase[:shift], obase[shift + blk.n_dst * f:]])
                 assert bool((rest == 7.0).all())  # nothing beside the rows is written
+
+
+# Outputs above 32 MiB bypass the caches; a count known to the host gets a
+# workgroup for every few rows.
+@pytest.mark.parametrize("rows,dim,tdt,odt", [
+    (83_886, 100, torch.float32, torch.float32), (83_887, 100, torch.float32, torch.float32),
+    (167_773, 100, torch.float32, torch.bfloat16), (90_001, 256, torch.float16, torch.float32),
+    (70_001, 256, torch.float16, torch.bfloat16), (66_000, 260, torch.bfloat16, torch.bfloat16)])
+def test_gather_large_outputs(rows, dim, tdt, odt):
+    g = torch.Generator(device=DEV).manual_seed(rows)
+    table = torch.randn((50_000, dim), generator=g, device=DEV).to(tdt)
+    table[7, :4] = torch.tensor([float("nan"), float("inf"), -0.0, 1e-30], device=DEV).to(tdt)
+    ids = torch.randint(0, 50_000, (rows,), generator=g, device=DEV)
+    ids[-1] = 7
+    out = torch.full((rows + 1, dim), 3.0, dtype=odt, device=DEV)
+    gnn.gather_features(table, ids, out[:rows])
+    want = table[ids].to(odt)
+    bits = torch.int32 if odt == torch.float32 else torch.int16
+    same = (out[:rows].view(bits) == want.view(bits)) | (torch.isnan(out[:rows]) & torch.isnan(want))
+    assert bool(same.all()) and bool((out[rows] == 3.0).all())
