@@ -407,7 +407,9 @@ def update_fwd(a_self: torch.Tensor, a_nbr: Optional[torch.Tensor], w: torch.Ten
     if ws is None and split:
         nb = _sz()
         _check(lib().gnn_update_fwd_workspace_size(K, w.shape[1], cap, gemm_dtype, ctypes.byref(nb)))
-        ws = torch.zeros(max(nb.value, 256), dtype=torch.uint8, device=a_self.device)
+        # (no state lives in a workspace, so it is not cleared: for a wide
+        # layer of 26,624 rows that was a 59 MB fill per call)
+        ws = _aligned_empty(nb.value, a_self.device)
     _check(lib().gnn_update_fwd(_ptr(a_self), _ptr(a_nbr), dtype_code(a_self.dtype), a_self.shape[1], _ptr(m_dev), cap,
                                 _ptr(w), _ptr(wt), _ptr(bias), w.shape[1], int(relu), gemm_dtype, _ptr(out),
                                 dtype_code(out.dtype), _ptr(ws), ws.numel() if ws is not None else 0,
