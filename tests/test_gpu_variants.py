@@ -248,3 +248,32 @@ def test_gather_large_outputs(rows, dim, tdt, odt):
     bits = torch.int32 if odt == torch.float32 else torch.int16
     same = (out[:rows].view(bits) == want.view(bits)) | (torch.isnan(out[:rows]) & torch.isnan(want))
     assert bool(same.all()) and bool((out[rows] == 3.0).all())
+
+
+# Gradients above 32 MiB bypass the caches.
+@pytest.mark.parametrize("n_src", [8192, 8193])
+@pytest.mark.parametrize("kind", ["mean", "max"])
+def test_aggregate_bwd_large_gradient(kind, n_src):
+    from tests.test_gpu_parity import relerr, upload_block
+    f, n_dst = 1024, 50
+    rng = np.random.default_rng(n_src)
+    rows = [rng.choice(n_src, size=40, replace=False) for _ in range(n_dst)] + [[] for _ in range(n_src - n_dst)]
+    rowptr, col = csr(rows)
+    blk = oracle.build_block(rowptr, col, np.arange(n_dst, dtype=np.int64), 40, 1, 1, 1)
+    # every vertex a source, so that the gradient is n_src rows
+    blk.src_ids = np.arange(n_src, dtype=np.int64)
+    blk.cscptr = np.concatenate([blk.cscptr, np.full(n_src + 1 - blk.cscptr.size, blk.cscptr[-1])])
+    b = upload_block(blk)
+    d_a = rng.standard_normal((n_dst, 2 * f)).astype(np.float32)
+    h = rng.standard_normal((n_src, f)).astype(np.float32)
+    d_src = torch.full((n_src + 1, f), 5.0, device=DEV)
+    h_d, d_a_d = torch.from_numpy(h).to(DEV), torch.from_numpy(d_a).to(DEV)
+    if kind == "max":
+        _, arg = oracle.aggregate_fwd_max(blk, h, oracle.F32)
+        want = oracle.aggregate_bwd_max(blk, arg, d_a, f, h, oracle.F64)
+        gnn.aggregate_bwd_max(b, torch.from_numpy(arg).to(DEV), d_a_d, f, d_src, h_d)
+    else:
+        want = oracle.aggregate_bwd(oracle.SAGE, blk, None, d_a, f, h, oracle.F64)
+        gnn.aggregate_bwd(b, gnn.GNN_AGG_SAGE_MEAN, d_a_d, f, d_src, h_d)
+    assert relerr(d_src[:n_src].cpu().numpy(), want) <= 1e-6  # fp32 sums of a few terms
+    assert bool((d_src[n_src] == 5.0).all())
