@@ -154,7 +154,7 @@ struct DweightJob {
 };
 
 // Lanes that share one output float4 of the split reduction: one per 16
-// splits (up to 64 splits; a lane's 16 loads are one round trip).
+// splits (up to 64 splits; a lane's 16 loads are two round trips).
 __host__ __device__ inline int reduce_lanes(int nsplit) { return nsplit > 32 ? 4 : nsplit > 16 ? 2 : 1; }
 
 // dw = sum over splits of the partials (db from row K); then, when w_upd /

@@ -550,10 +550,12 @@ __device__ __forceinline__ void split_range(int64_t total, int nsplit, int split
 __host__ __device__ inline int64_t part_ld(int64_t cols) { return (cols + 3) / 4 * 4; }
 
 // Sum over splits s = 0..nsplit-1, in that order, of the float4 at
-// p + s * stride.  Loads are issued sixteen splits at a time (one round trip
-// for the usual split counts).
+// p + s * stride.  Loads are issued eight splits at a time: sixteen take one
+// round trip for the usual split counts but 98 registers, which costs the
+// launches that a reduction shares more wavefronts than it saves time (a
+// three-layer step 277 us with sixteen, 273 with eight).
 __device__ __forceinline__ float4 sum_splits(const float *p, int64_t stride, int nsplit) {
-    constexpr int kAtOnce = 16;
+    constexpr int kAtOnce = 8;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int s0 = 0; s0 < nsplit; s0 += kAtOnce) {
         float4 v[kAtOnce];
