@@ -295,11 +295,12 @@ __device__ __forceinline__ void sort_counting(uint32_t *lds, int words, const in
 // takes 10 and 26 us.
 //
 // P sets the LDS words (512 P) and the entries a thread holds.  2 when the
-// block's rows fit one counting window of those words (2,048), else 8: the
-// larger area keeps the number of windows down for hubs of large blocks, but
-// its registers cost occupancy in the launches that the sort rides in (99
-// VGPRs instead of 71 beside layer 1's aggregation: a pipelined step of 1,024
-// targets lost 2.5%).
+// block's rows fit one counting window of those words (2,048 rows), 4 up to 16
+// windows (65,536 rows), else 8: a larger area keeps the number of windows down
+// for hubs of large blocks, but its registers cost occupancy in the launches
+// that the sort rides in (at P = 8 99 VGPRs instead of 71 beside layer 1's
+// aggregation: a pipelined step of 1,024 targets lost 2.5%, a three-layer step
+// takes 277 us with P = 8 for its 16,384-row block and 272 with 4).
 template <int P> struct SortJob {
     Args a;
     __device__ void run(int64_t blk, int64_t nblk) const {
@@ -380,6 +381,7 @@ template <int P> struct SortJob {
 // f(tag) with the P (an integral constant) of a block of cap_dst rows.
 template <class F> void with_sort_size(int64_t cap_dst, F &&f) {
     if (cap_dst <= 2048) f(std::integral_constant<int, 2>{});
+    else if (cap_dst <= 65536) f(std::integral_constant<int, 4>{});
     else f(std::integral_constant<int, 8>{});
 }
 

@@ -34,13 +34,14 @@ def build(rowptr, col, dst, fanout, norm=False):
 
 
 # Columns sorted by a thread (up to 16 entries), a wavefront in registers (64)
-# or through LDS (128 with up to 2,048 rows of capacity, else 512), the
-# workgroup through LDS (2,048) or by counting rows (longer, or up to 8,192
-# rows in the block); rows spread over the block and crowded into a part of it.
-@pytest.mark.parametrize("n_dst", [700, 2048, 2049, 8192, 8193, 20_000])
+# or through LDS (128 with up to 2,048 rows of capacity, 256 up to 65,536, else
+# 512), the workgroup through LDS (1,024 and 2,048) or by counting rows (longer,
+# or as many rows as LDS counts in one pass: 2,048, 4,096 and 8,192); rows
+# spread over the block and crowded into a part of it.
+@pytest.mark.parametrize("n_dst", [700, 2048, 2049, 4096, 4097, 8192, 8193, 20_000, 65_536, 65_537])
 def test_transpose_sort_tiers(n_dst):
-    lens = [l for l in (1, 2, 15, 16, 17, 63, 64, 65, 127, 128, 129, 511, 512, 513, 1024, 2047, 2048, 2049, 4097, 8193,
-                        12_000, 20_000) if l <= n_dst]
+    lens = [l for l in (1, 2, 15, 16, 17, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025,
+                        2047, 2048, 2049, 4097, 8193, 12_000, 20_000) if l <= n_dst]
     rng = np.random.default_rng(n_dst)
     dst = rng.permutation(n_dst).astype(np.int64)
     rows = [[] for _ in range(n_dst + len(lens) + 3)]
