@@ -553,7 +553,12 @@ WideBwdPlan plan_wide_bwd(int64_t K, int64_t n_out, int64_t cap_m) {
 }
 
 bool wide_bwd_shape(int64_t K, int64_t n_out, int64_t cap_m, int gemm_dt) {
-    return gemm_dt == GNN_BF16 && wide_layer(K, n_out, cap_m) && n_out % 8 == 0 && K % 8 == 0;
+    // A tall layer whose single split does not fit the allocation-free entry's
+    // scratch stays with the engine, whose partials may (344 x 16,384: 22.6 MB of
+    // partials there, 33.9 MB here with W's bf16 copy).
+    const bool fits = wide_shape(K, n_out) || (K + 1) * part_ld(n_out) * 4 + wb_bytes(K, n_out) + 256 <=
+                                                  int64_t(GNN_UPDATE_BWD_NOALLOC_MAX_SCRATCH);
+    return gemm_dt == GNN_BF16 && wide_layer(K, n_out, cap_m) && n_out % 8 == 0 && K % 8 == 0 && fits;
 }
 
 bool wide_bwd_ok(const Args &a) {

@@ -300,3 +300,19 @@ def test_sampler_fault_hook_validation(gnn):
     assert lib.gnn_debug_sampler_fault(1, 0) == gnn.GNN_EINVAL
     assert lib.gnn_debug_sampler_fault(1, 64) == gnn.GNN_OK
     assert lib.gnn_debug_sampler_fault(-1, 0) == gnn.GNN_OK  # back to normal
+
+
+@pytest.mark.parametrize("k, n_out, cap", [(344, 16384, 257), (384, 16384, 8192), (16384, 336, 16384),
+                                           (16384, 384, 4096), (512, 256, 45_056), (264, 192, 1 << 20)])
+def test_tall_layer_backward_scratch_fits_the_allocation_free_entry(gnn, k, n_out, cap):
+    """A layer that many rows alone would bring to the wide kernels needs no more
+    than the allocation-free entry's 32 MiB where the engine's partials (the
+    fp32 call's size: same tiles and splits) fit in it."""
+    lib, nb = gnn.lib(), ctypes.c_size_t()
+    size = {}
+    for dt in (gnn.GNN_F32, gnn.GNN_BF16):
+        assert lib.gnn_update_bwd_workspace_size(k, n_out, cap, dt, ctypes.byref(nb)) == gnn.GNN_OK
+        size[dt] = nb.value
+    limit = 32 << 20
+    assert size[gnn.GNN_F32] <= limit
+    assert size[gnn.GNN_BF16] <= limit
