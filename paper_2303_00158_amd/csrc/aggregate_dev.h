@@ -270,12 +270,20 @@ __device__ __forceinline__ void agg_fwd_rows(const Edges &edges, const int64_t *
 //
 // A source's edges are added one after another, four loads in flight; a row
 // takes ceil(f / 4) lanes, so rows of up to 128 elements share a wavefront
-// (RowLanes). Most sources have one or two edges: the kernel is a chain of
+// (RowLanes) and are summed four edges at a time, in two pairs: one running
+// sum over all edges was further from the 64-bit result (1.8e-8 against
+// 1.6e-8, 246 targets, f = 128) than sums over alternate edges. Most sources have one or two edges: the kernel is a chain of
 // three dependent loads per row (column pointer, rows, their gradients), so what
 // counts is that many rows are in flight (8,192 targets, f = 256: 32 us with indices and
 // weights taken from other lanes at 75 registers, now 28 us; the maximum's 43
 // us, now 41).
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ void add4(float4 &acc, const float4 &a, const float4 &b) {
+    acc.x += a.x + b.x;
+    acc.y += a.y + b.y;
+    acc.z += a.z + b.z;
+    acc.w += a.w + b.w;
+}
 // This lane's column j, its edges beg .. beg + len - 1. UNI: one column per
 // wavefront (C > 32), whose indices are kept scalar.
 template <bool UNI> __device__ __forceinline__ int32_t maybe_scalar(int32_t x) {
@@ -317,9 +325,17 @@ __device__ __forceinline__ void agg_bwd_rows(int64_t n_dst, const int64_t *__res
                     else
                         w[q] = 1.f / static_cast<float>(rowptr[i[q] + 1] - rowptr[i[q]]);
                 }
+            if constexpr (UNI) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (t + q < len) fma4(acc, w[q], v[q]);
+                for (int q = 0; q < 4; ++q)
+                    if (t + q < len) fma4(acc, w[q], v[q]);
+            } else {
+                float4 pair[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (t + q < len) fma4(pair[q / 2], w[q], v[q]);
+                add4(acc, pair[0], pair[1]);
+            }
         }
         if (j < n_dst) {
             const float ws = (KIND == GNN_AGG_GCN_SYM) ? wj * wj : 1.f;
@@ -386,7 +402,7 @@ __device__ __forceinline__ void walk_columns(const gnn_block &b, int64_t blk, in
     }
 }
 
-template <int KIND, class THB>
+template <int KIND, class THB, bool UNI>
 __device__ __forceinline__ void agg_bwd_long(int64_t n_dst, const int64_t *__restrict__ rowptr,
                                              const int32_t *__restrict__ cscrow, const float *__restrict__ src_norm,
                                              const float *__restrict__ d_a, int64_t f, const THB *__restrict__ h_below,
@@ -421,7 +437,16 @@ __device__ __forceinline__ void agg_bwd_long(int64_t n_dst, const int64_t *__res
                     v[u] = (d_a + i * ka + nbr_off)[e];
                 }
 #pragma unroll
-                for (int u = 0; u < kLongAhead; ++u) acc = fmaf(w[u], tb + u < wn ? v[u] : 0.f, acc);
+                for (int u = 0; u < kLongAhead; ++u) v[u] = tb + u < wn ? v[u] : 0.f;
+                if constexpr (UNI) {
+#pragma unroll
+                    for (int u = 0; u < kLongAhead; ++u) acc = fmaf(w[u], v[u], acc);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < kLongAhead; u += 4)
+                        acc += fmaf(w[u + 1], v[u + 1], fmaf(w[u], v[u], 0.f)) +
+                               fmaf(w[u + 3], v[u + 3], fmaf(w[u + 2], v[u + 2], 0.f));
+                }
             }
         }
         if (j < n_dst) acc = fmaf((KIND == GNN_AGG_GCN_SYM) ? wj * wj : 1.f, self, acc);
@@ -493,7 +518,7 @@ struct BwdJob {
                                                       d_src, j, beg, len);
             },
             [&](int64_t j, int64_t beg, int64_t end) {
-                agg_bwd_long<KIND, THB>(n_dst, b.rowptr, b.cscrow, b.src_norm, d_a, f, h_below, d_src, j, beg, end);
+                agg_bwd_long<KIND, THB, UNI>(n_dst, b.rowptr, b.cscrow, b.src_norm, d_a, f, h_below, d_src, j, beg, end);
             });
     }
     __device__ void run(int64_t blk, int64_t nblk) const {
@@ -663,14 +688,17 @@ __device__ __forceinline__ void agg_bwd_rows_max(int64_t n_dst, const int32_t *_
                 if (a[q].x | a[q].y | a[q].z | a[q].w)
                     v[q] = load_chunk<VEC>(d_a + (static_cast<int64_t>(i[q]) * ka + f), 0, e0, f);
             }
+            float4 pair[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};  // (as agg_bwd_rows)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 if (t + q >= len || !(a[q].x | a[q].y | a[q].z | a[q].w)) continue;
-                acc.x += a[q].x ? v[q].x : 0.f;
-                acc.y += a[q].y ? v[q].y : 0.f;
-                acc.z += a[q].z ? v[q].z : 0.f;
-                acc.w += a[q].w ? v[q].w : 0.f;
+                float4 &sum = UNI ? acc : pair[q / 2];
+                sum.x += a[q].x ? v[q].x : 0.f;
+                sum.y += a[q].y ? v[q].y : 0.f;
+                sum.z += a[q].z ? v[q].z : 0.f;
+                sum.w += a[q].w ? v[q].w : 0.f;
             }
+            if constexpr (!UNI) add4(acc, pair[0], pair[1]);
         }
         if (j < n_dst) {
             acc.x += self.x;
@@ -690,7 +718,7 @@ __device__ __forceinline__ void agg_bwd_rows_max(int64_t n_dst, const int32_t *_
 
 // A long column of the maximum's backward, by the whole workgroup
 // (agg_bwd_long's split and order).
-template <class THB>
+template <class THB, bool UNI>
 __device__ __forceinline__ void agg_bwd_long_max(int64_t n_dst, const int32_t *__restrict__ cscrow,
                                                  const int32_t *__restrict__ argmax, const float *__restrict__ d_a,
                                                  int64_t f, const THB *__restrict__ h_below,
@@ -725,8 +753,13 @@ __device__ __forceinline__ void agg_bwd_long_max(int64_t n_dst, const int32_t *_
                     v[u] = 0.f;
                     if (i >= 0 && a[u] == jj) v[u] = (d_a + i * ka + f)[e];
                 }
+                if constexpr (UNI) {
 #pragma unroll
-                for (int u = 0; u < kLongAhead; ++u) acc += v[u];
+                    for (int u = 0; u < kLongAhead; ++u) acc += v[u];
+                } else {
+#pragma unroll
+                    for (int u = 0; u < kLongAhead; u += 4) acc += (v[u] + v[u + 1]) + (v[u + 2] + v[u + 3]);
+                }
             }
         }
         if (j < n_dst) acc += self;
@@ -769,7 +802,7 @@ struct BwdMaxJob {
                 agg_bwd_rows_max<THB, VEC, UNI, NT>(n_dst, b.cscrow, argmax, d_a, f, C, L, h_below, d_src, j, beg, len);
             },
             [&](int64_t j, int64_t beg, int64_t end) {
-                agg_bwd_long_max<THB>(n_dst, b.cscrow, argmax, d_a, f, h_below, d_src, j, beg, end);
+                agg_bwd_long_max<THB, UNI>(n_dst, b.cscrow, argmax, d_a, f, h_below, d_src, j, beg, end);
             });
     }
     __device__ void run(int64_t blk, int64_t nblk) const {
