@@ -380,8 +380,9 @@ gnn_status gnn_two_layer_fwd_max(const gnn_block *last, int32_t fanout, const vo
  *           kept between calls; calls sharing it must not overlap).
  * dw1, db1, dw2 and db2 equal, bit for bit, gnn_aggregate_bwd (dA^2 -> G^1,
  * h_below = h1) followed by gnn_update_bwd on each layer with the same caps
- * (cap_m1 for layer 1, last->cap_dst for layer 2).  Needs f1 % 4 == 0 and
- * f1 > 128, K1 <= 256, f0 % 4 == 0, 8-byte aligned bf16 rows and h1;
+ * (cap_m1 for layer 1, last->cap_dst for layer 2); where gnn_update_bwd takes
+ * its wide kernels for a tall layer 2, dw2 and db2 are the same sums in
+ * another order.  Needs f1 % 4 == 0 and f1 > 128, K1 <= 256, f0 % 4 == 0, 8-byte aligned bf16 rows and h1;
  * else GNN_EUNSUPPORTED.
  * ------------------------------------------------------------------------ */
 gnn_status gnn_two_layer_bwd_workspace_size(gnn_agg kind, int64_t f0, int64_t f1, int64_t n_out, int64_t cap_m1,

@@ -16,8 +16,10 @@ TwoBwdPlan plan_two_bwd(int kind, const gnn_block &b2, const void *x_self, const
                       b2.cap_dst, w2, g2, n_out, GNN_BF16, dw2, db2, nullptr, part2, w2_upd, b2_upd, wt2_upd, lr};
     t.a1 = gbwd::Args{sage ? x_self : m1, sage ? m1 : nullptr, GNN_BF16, f0, m1_rows, cap_m1, w1, nullptr, f1,
                       GNN_BF16, dw1, db1, nullptr, part1, w1_upd, b1_upd, wt1_upd, lr};
-    t.p2 = gbwd::plan(t.a2);
-    t.p1 = gbwd::plan(t.a1);
+    // (the engine's jobs also for a tall layer that gnn_update_bwd gives to the
+    // wide kernels: this launch computes layer 2's partials with a DweightJob)
+    t.p2 = gbwd::plan_engine(t.a2);
+    t.p1 = gbwd::plan_engine(t.a1);
     t.gemm_ok = t.p2.bf && t.p1.bf && t.p2.pw.tile == 64 && t.p1.pw.tile == 64 && t.p2.vec_a && t.p1.vec_a &&
                 t.p2.pw.map.blocks() <= kMaxGrid && t.p1.pw.map.blocks() <= kMaxGrid;
     // The folded job repeats the aggregation backward's arithmetic when that

@@ -291,7 +291,16 @@ struct Plan {
     unsigned din_grid, dw_grid, red_grid;
 };
 
-inline Plan plan(const Args &a) {
+// Workgroups of the reduction job.
+inline unsigned reduce_grid(const Args &a, int nsplit) {
+    const int64_t work = (a.K() + 1) * (part_ld(a.n_out) / 4) * reduce_lanes(nsplit);
+    return static_cast<unsigned>(std::min<int64_t>(ceil_div(work, 256), 1 << 20));
+}
+
+// The plan of the engine's jobs below, whatever the layer's size.  Callers that
+// launch a DweightJob themselves take this one: its partials and its
+// reduction have one split count, pw.map's.
+inline Plan plan_engine(const Args &a) {
     Plan p;
     const int64_t K = a.K();
     p.bf = a.gemm_dt == GNN_BF16;
@@ -301,17 +310,25 @@ inline Plan plan(const Args &a) {
     p.vec_o = (K % 4 == 0) && aligned(a.d_a, 16);
     p.vec_r = (a.n_out % 4 == 0) && aligned(a.dw, 16) && aligned(a.db, 16) && aligned(a.w_upd, 16) &&
               aligned(a.b_upd, 16);
+    p.wide = false;
     p.pa = plan_dinput(a.cap_m, K);
     p.pw = plan_dw(K, a.n_out, a.cap_m, p.bf);
-    p.wide = wide_bwd_ok(a);
-    if (p.wide) {
-        const WideBwdPlan w = plan_wide_bwd(K, a.n_out, a.cap_m);
-        p.pw.nsplit = static_cast<int>(a.d_a ? w.nsplit_da : w.nsplit);
-    }
     p.din_grid = (a.d_a && a.cap_m > 0) ? static_cast<unsigned>(p.pa.map.blocks()) : 0;
     p.dw_grid = static_cast<unsigned>(p.pw.map.blocks());
-    const int64_t work = (K + 1) * (part_ld(a.n_out) / 4) * reduce_lanes(p.pw.nsplit);
-    p.red_grid = static_cast<unsigned>(std::min<int64_t>(ceil_div(work, 256), 1 << 20));
+    p.red_grid = reduce_grid(a, p.pw.nsplit);
+    return p;
+}
+
+// The plan of launch_update_bwd_gemms and its reduction: the wide kernels
+// where they apply, with their own split count.
+inline Plan plan(const Args &a) {
+    Plan p = plan_engine(a);
+    p.wide = wide_bwd_ok(a);
+    if (p.wide) {
+        const WideBwdPlan w = plan_wide_bwd(a.K(), a.n_out, a.cap_m);
+        p.pw.nsplit = static_cast<int>(a.d_a ? w.nsplit_da : w.nsplit);
+        p.red_grid = reduce_grid(a, p.pw.nsplit);
+    }
     return p;
 }
 

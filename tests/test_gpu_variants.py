@@ -278,3 +278,52 @@ def test_aggregate_bwd_large_gradient(kind, n_src):
         gnn.aggregate_bwd(b, gnn.GNN_AGG_SAGE_MEAN, d_a_d, f, d_src, h_d)
     assert relerr(d_src[:n_src].cpu().numpy(), want) <= 1e-6  # fp32 sums of a few terms
     assert bool((d_src[n_src] == 5.0).all())
+
+
+# A last layer tall and wide enough that gnn_update_bwd gives it to the 256 x 256
+# tiles: the folded two-layer backward keeps the engine's splits for it.
+@pytest.mark.parametrize("kind,f1,n_out,n_dst", [("mean", 256, 256, 32_513), ("max", 256, 200, 32_700),
+                                                 ("gcn", 264, 256, 33_000)])
+def test_two_layer_bwd_tall_last_layer(kind, f1, n_out, n_dst):
+    rng = np.random.default_rng(n_dst)
+    n, f0, fanout = 36_000, 64, 3
+    g = torch.Generator(device=DEV).manual_seed(n_dst)
+    rowptr = np.arange(n + 1, dtype=np.int64) * 4
+    col = np.sort(rng.integers(0, n, size=(n, 4)), axis=1).reshape(-1).astype(np.int64)
+    graph = gnn.DeviceGraph(torch.from_numpy(rowptr).to(DEV), torch.from_numpy(col).to(DEV))
+    b = gnn.DeviceBlock(n, n_dst, fanout, True, True, DEV)
+    gnn.build_block(graph, torch.from_numpy(rng.permutation(n)[:n_dst].astype(np.int64)).to(DEV), fanout, 1, 0, 1, b,
+                    gnn.sampler_workspace(n, n_dst, fanout, DEV), gcn_norm_t=gnn.gcn_norm(graph))
+    n_src = int(b.counts[1])
+    mk = lambda *s: torch.randn(s, generator=g, device=DEV)  # noqa
+    cat = kind != "gcn"
+    x, m1 = mk(n, f0).bfloat16(), mk(n, f0).bfloat16()
+    h1, agg = mk(b.src_ids.numel(), f1).clamp_(min=0).bfloat16(), mk(n_dst, f1).bfloat16()
+    d_a, g2 = mk(n_dst, 2 * f1 if cat else f1), mk(n_dst, n_out)
+    arg = torch.zeros((n_dst, f1), dtype=torch.int32, device=DEV)
+    K1, K2 = (2 * f0, 2 * f1) if cat else (f0, f1)
+    out = [torch.empty((K1, f1), device=DEV), torch.empty(f1, device=DEV), torch.empty((K2, n_out), device=DEV),
+           torch.empty(n_out, device=DEV)]
+    rows = torch.tensor([n_src], dtype=torch.int64, device=DEV)
+    cap1 = b.src_ids.numel()
+    gk = {"mean": gnn.GNN_AGG_SAGE_MEAN, "gcn": gnn.GNN_AGG_GCN_SYM, "max": gnn.GNN_AGG_SAGE_MAX}[kind]
+    ws = gnn.two_layer_bwd_workspace(gk, f0, f1, n_out, cap1, n_dst, DEV)
+    ws.fill_(255)  # NaN patterns
+    print(f"[two_layer_bwd tall] {kind} f1={f1} n_out={n_out} n_dst={n_dst}", flush=True)
+    g1 = torch.empty((b.src_ids.numel(), f1), device=DEV)
+    if kind == "max":
+        gnn.aggregate_fwd_max(b, h1, torch.empty_like(agg), arg)
+        gnn.two_layer_bwd_max(b, x, m1, rows, cap1, h1, agg, arg, d_a, g2, *out, ws=ws)
+        gnn.aggregate_bwd_max(b, arg, d_a, f1, g1, h1)
+    else:
+        gnn.two_layer_bwd(b, gk, x if cat else None, m1, rows, cap1, h1, agg, d_a, g2, *out, ws=ws)
+        gnn.aggregate_bwd(b, gk, d_a, f1, g1, h1)
+    dw1, db1 = torch.empty_like(out[0]), torch.empty_like(out[1])
+    gnn.update_bwd(x if cat else m1, m1 if cat else None, torch.zeros((K1, f1), device=DEV), g1, dw1, db1, None,
+                   gnn.GNN_BF16, m_dev=rows)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], dw1) and torch.equal(out[1], db1)
+    A = torch.cat([h1[:n_dst], agg], 1).double() if cat else agg.double()
+    tol = 4 * 2.0 ** -24 * n_dst ** 0.5  # fp32 sums of n_dst terms, 4 x for the spread
+    for got, want in ((out[2], A.t() @ g2.bfloat16().double()), (out[3], g2.double().sum(0))):
+        assert float((got.double() - want).norm() / want.norm()) <= tol
