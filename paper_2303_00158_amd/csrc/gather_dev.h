@@ -23,32 +23,19 @@ struct Args {
     int64_t cap, dim;
     void *out;
 };
-// An output larger than the L2s is not at hand for whoever reads it next: rows
-// and output then bypass them (non-temporal; the jobs' STREAM), which leaves
-// the L2s to rows that repeat. 334,699 rows of 100 fp32 values to bf16: 47.6 us
-// with cached accesses, 44.1 us so; the training step's small X', read by the
-// next launches, loses by it (553 to 556 us for 8 steps).
-constexpr int64_t kStreamBytes = 32 << 20;
 
 template <class T> struct Raw4;
 template <> struct Raw4<float> { using type = uint4; };
 template <> struct Raw4<uint16_t> { using type = uint2; };
 
-// A 4-element chunk of either width, through the caches or past them.
-template <bool STREAM, class V> __device__ __forceinline__ V load_raw(const void *p) {
-    typedef uint32_t words __attribute__((ext_vector_type(sizeof(V) / 4)));
-    const words *w = static_cast<const words *>(p);
-    if constexpr (STREAM) return __builtin_bit_cast(V, __builtin_nontemporal_load(w));
-    return __builtin_bit_cast(V, *w);
-}
-template <bool STREAM, class V> __device__ __forceinline__ void store_raw(void *p, const V &v) {
-    typedef uint32_t words __attribute__((ext_vector_type(sizeof(V) / 4)));
-    words *w = static_cast<words *>(p);
-    if constexpr (STREAM)
-        __builtin_nontemporal_store(__builtin_bit_cast(words, v), w);
-    else
-        *w = __builtin_bit_cast(words, v);
-}
+// A 4-element chunk of either width. Always through the caches: accesses past
+// them (non-temporal, for outputs above 32 MiB) made the call alone shorter on
+// new distinct ids (334,699 rows of 100 fp32 values to bf16: 47.7 us, 44.2 so),
+// but the output's reader paid for it and rows that repeat were fetched again:
+// 143,602 fp32 rows and their aggregation took 54.8 us instead of 46.8, 334,699
+// ids of a 10,000-row table 35.3 instead of 22.8.
+template <class V> __device__ __forceinline__ V load_raw(const void *p) { return *static_cast<const V *>(p); }
+template <class V> __device__ __forceinline__ void store_raw(void *p, const V &v) { *static_cast<V *>(p) = v; }
 
 // Four values in the output's type.
 template <class T> __device__ __forceinline__ typename Raw4<T>::type narrow4(const float4 &v) {
@@ -127,7 +114,7 @@ __device__ __forceinline__ void gather_rows(const Args &a, const RowSlots &rs, i
 }
 
 // Same element type on both sides: bit copy of 4-element chunks.
-template <class T, bool STREAM>
+template <class T>
 struct Copy4 {
     Args a;
     RowSlots rs;
@@ -136,12 +123,12 @@ struct Copy4 {
         const T *__restrict__ table = static_cast<const T *>(a.table);
         T *__restrict__ out = static_cast<T *>(a.out);
         gather_rows(
-            a, rs, blk, nblk, [&](int64_t off) { return load_raw<STREAM, R>(table + off); },
-            [&](int64_t off, R v) { store_raw<STREAM>(out + off, v); });
+            a, rs, blk, nblk, [&](int64_t off) { return load_raw<R>(table + off); },
+            [&](int64_t off, R v) { store_raw(out + off, v); });
     }
 };
 
-template <bool SRC_F16, class TOut, bool STREAM>
+template <bool SRC_F16, class TOut>
 struct Convert4 {
     Args a;
     RowSlots rs;
@@ -150,13 +137,13 @@ struct Convert4 {
         if constexpr (SRC_F16) {
             const uint16_t *__restrict__ table = static_cast<const uint16_t *>(a.table);
             gather_rows(
-                a, rs, blk, nblk, [&](int64_t off) { return load_raw<STREAM, uint2>(table + off); },
-                [&](int64_t off, uint2 v) { store_raw<STREAM>(out + off, narrow4<TOut>(widen_f16(v))); });
+                a, rs, blk, nblk, [&](int64_t off) { return load_raw<uint2>(table + off); },
+                [&](int64_t off, uint2 v) { store_raw(out + off, narrow4<TOut>(widen_f16(v))); });
         } else {
             const float *__restrict__ table = static_cast<const float *>(a.table);
             gather_rows(
-                a, rs, blk, nblk, [&](int64_t off) { return load_raw<STREAM, float4>(table + off); },
-                [&](int64_t off, float4 v) { store_raw<STREAM>(out + off, narrow4<TOut>(v)); });
+                a, rs, blk, nblk, [&](int64_t off) { return load_raw<float4>(table + off); },
+                [&](int64_t off, float4 v) { store_raw(out + off, narrow4<TOut>(v)); });
         }
     }
 };
@@ -234,16 +221,16 @@ inline bool vec_ok(const Args &a, int tdt, int odt) {
 }
 
 // Calls f(job) with the job of the variant serving tdt -> odt; returns false
-// when the pair is not supported.  STREAM applies to the vector variants.
-template <bool STREAM = false, class F>
+// when the pair is not supported.
+template <class F>
 bool with_job(const Args &a, int tdt, int odt, F &&f) {
     if (vec_ok(a, tdt, odt)) {
         const RowSlots rs = RowSlots::of(a.dim);
-        if (tdt == odt && tdt == GNN_F32) return f(Copy4<float, STREAM>{a, rs}), true;
-        if (tdt == odt) return f(Copy4<uint16_t, STREAM>{a, rs}), true;
-        if (tdt == GNN_F32 && odt == GNN_BF16) return f(Convert4<false, uint16_t, STREAM>{a, rs}), true;
-        if (tdt == GNN_F16 && odt == GNN_BF16) return f(Convert4<true, uint16_t, STREAM>{a, rs}), true;
-        if (tdt == GNN_F16 && odt == GNN_F32) return f(Convert4<true, float, STREAM>{a, rs}), true;
+        if (tdt == odt && tdt == GNN_F32) return f(Copy4<float>{a, rs}), true;
+        if (tdt == odt) return f(Copy4<uint16_t>{a, rs}), true;
+        if (tdt == GNN_F32 && odt == GNN_BF16) return f(Convert4<false, uint16_t>{a, rs}), true;
+        if (tdt == GNN_F16 && odt == GNN_BF16) return f(Convert4<true, uint16_t>{a, rs}), true;
+        if (tdt == GNN_F16 && odt == GNN_F32) return f(Convert4<true, float>{a, rs}), true;
         return false;
     }
     if (tdt == GNN_F32 && odt == GNN_F32) return f(Scalar<GNN_F32, GNN_F32>{a}), true;
