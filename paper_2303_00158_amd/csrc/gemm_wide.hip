@@ -25,8 +25,8 @@
 //  * LDS rows are 64 bytes (32 bf16); their four 16-byte granules are
 //    XOR-swizzled by bits 1..2 of the row, so that the fragment reads (16
 //    rows of one granule) are free of bank conflicts;
-//  * tiles are dealt to the eight XCDs in contiguous ranges of the
-//    row-major tile order, so the workgroups on one XCD share A rows (and
+//  * the tiles that hold rows are dealt to the eight XCDs in contiguous ranges
+//    of the row-major tile order, so the workgroups on one XCD share A rows (and
 //    all of W^T) in that XCD's L2;
 //  * tiles are 224 or 192 rows high instead of 256 (wavefronts of 112 x 64 or
 //    96 x 64) where that fills the CUs' last round better: the kernel's time goes by
@@ -65,7 +65,7 @@ struct WideArgs {
     const float *bias;        // n_out, or null
     int relu;
     void *out;                // cap_m x n_out, bf16 or fp32
-    int64_t tiles_m, tiles_n, per_xcd;
+    int64_t tiles_n;
     float *part;              // split partial tiles, or null (no split)
     int64_t grid;             // the launch's workgroups
 };
@@ -181,35 +181,33 @@ __device__ __forceinline__ void mma_chunk(f32x4 (&acc)[FI][Layout<NW>::WJ], cons
     __builtin_amdgcn_sched_group_barrier(0x008, FI, 0);
 }
 
-// FI A fragments per wavefront: tiles of 32 FI rows (256 or 224) by 256
-// columns.  The copies always fill 256 LDS rows; with 224-row tiles the last
-// 32 are the next tile's rows (or zeros past the capacity) and go unused.
+// The stages of the LDS ring: separate arrays, so that the compiler sees that
+// reads of one do not wait for copies to the others.
+typedef uint16_t Stage[2][kTileElems];
+
+// One tile of 32 FI rows (FI A fragments per wavefront: 256, 224 or 192) by
+// 256 columns.  The copies always fill 256 LDS rows; with lower tiles the last
+// 32 or 64 are the next tile's rows (or zeros past the capacity) and go unused.
 template <int NW, int FI, class TO>
-__global__ void __launch_bounds__(NW * 64, 1) wide_fwd_kernel(WideArgs p) {
+__device__ __forceinline__ void wide_fwd_tile(const WideArgs &p, int64_t M, Stage &lds0, Stage &lds1, Stage &lds2,
+                                              Stage &lds3) {
     constexpr int TM = 32 * FI;
     using LY = Layout<NW>;
     constexpr int WJ = LY::WJ;
-    __shared__ __attribute__((aligned(16))) uint16_t lds0[2][kTileElems];
-    __shared__ __attribute__((aligned(16))) uint16_t lds1[2][kTileElems];
-    __shared__ __attribute__((aligned(16))) uint16_t lds2[2][kTileElems];
-    __shared__ __attribute__((aligned(16))) uint16_t lds3[2][kTileElems];
-    // tile of this workgroup: XCD x = blockIdx % 8 takes tiles
-    // [x * per_xcd, (x + 1) * per_xcd) of the row-major tile order.  With a
-    // split (few tiles hold rows), work item w = s T + t is split s of tile
-    // t, dealt to the XCDs the same way.
+    // tile of this workgroup: the T tiles that hold rows, in row-major order,
+    // are dealt to the XCDs (xcd_item).  With a split (few tiles hold rows),
+    // work item w = s T + t is split s of tile t.
     const int64_t b = blockIdx.x;
-    const int64_t M = p.m_dev ? min(*p.m_dev, p.cap_m) : p.cap_m;
     const int64_t T = ceil_div(M, int64_t(TM)) * p.tiles_n;
     const int64_t nch_all = p.K / kBK;
     const int S = p.part ? wide_split(T, nch_all / 4, p.grid) : 1;
     int64_t t, c_beg = 0, nch = nch_all;
     int split = 0;
+    const int64_t w = xcd_item(b, T * S);
+    if (w < 0) return;
     if (S == 1) {
-        t = (b % kXcds) * p.per_xcd + b / kXcds;
-        if (t >= p.tiles_m * p.tiles_n) return;
+        t = w;
     } else {
-        const int64_t w = (b % kXcds) * ceil_div(T * S, int64_t(kXcds)) + b / kXcds;
-        if (w >= T * S) return;
         split = static_cast<int>(w / T);
         t = w % T;
         nch = nch_all / S;
@@ -217,7 +215,6 @@ __global__ void __launch_bounds__(NW * 64, 1) wide_fwd_kernel(WideArgs p) {
     }
     const int64_t tm = t / p.tiles_n, tn = t % p.tiles_n;
     const int64_t row0 = tm * TM, col0 = tn * kTile;
-    if (row0 >= M) return;
 
     f32x4 acc[FI][WJ];
 #pragma unroll
@@ -315,6 +312,22 @@ __global__ void __launch_bounds__(NW * 64, 1) wide_fwd_kernel(WideArgs p) {
     }
 }
 
+// FI is the capacity's tile height.  Where fewer rows are live a lower tile may
+// take no more rounds of the CUs, and a round of 192 rows is shorter than one
+// of 256: 60,000 rows of capacity, 6,000 live, 512 x 192, 18.4 us, now 16.0.
+// (Splits keep one height: the reduction kernel reads their tiles.)
+template <int NW, int FI, class TO>
+__global__ void __launch_bounds__(NW * 64, 1) wide_fwd_kernel(WideArgs p) {
+    __shared__ __attribute__((aligned(16))) Stage lds0, lds1, lds2, lds3;
+    const int64_t M = p.m_dev ? min(*p.m_dev, p.cap_m) : p.cap_m;
+    if constexpr (FI > 6) {
+        const int64_t low = ceil_div(M, int64_t(192)) * p.tiles_n, high = ceil_div(M, int64_t(32 * FI)) * p.tiles_n;
+        if (!p.part && low <= p.grid && ceil_div(low, kCus) * 192 < ceil_div(high, kCus) * (32 * FI))
+            return wide_fwd_tile<NW, 6, TO>(p, M, lds0, lds1, lds2, lds3);
+    }
+    wide_fwd_tile<NW, FI, TO>(p, M, lds0, lds1, lds2, lds3);
+}
+
 // out = act(sum over the splits, in order, of the partial tiles + bias) for
 // the rows held on the device, when the forward kernel split (it decides the
 // same way from the same row count); else nothing.
@@ -381,7 +394,7 @@ namespace {
 // 1.6 rounds of 256 CUs, 476 fill 1.9; the shorter tiles finish sooner).
 struct WideGrid {
     int fi;
-    int64_t tiles_m, tiles_n, per_xcd, blocks;
+    int64_t tiles_n, blocks;
 };
 WideGrid wide_grid(int64_t cap_m, int64_t n_out) {
     WideGrid g{};
@@ -390,9 +403,7 @@ WideGrid wide_grid(int64_t cap_m, int64_t n_out) {
     g.fi = 8;
     for (int fi : {7, 6})
         if (cost(32 * fi) < cost(32 * g.fi)) g.fi = fi;
-    g.tiles_m = ceil_div(cap_m, int64_t(32 * g.fi));
-    g.per_xcd = ceil_div(g.tiles_m * g.tiles_n, kXcds);
-    g.blocks = g.per_xcd * kXcds;
+    g.blocks = round_up(ceil_div(cap_m, int64_t(32 * g.fi)) * g.tiles_n, int64_t(kXcds));
     return g;
 }
 
@@ -420,9 +431,7 @@ gnn_status launch_wide_fwd(const void *a_self, const void *a_nbr, int64_t k_each
     p.relu = relu;
     p.out = out;
     const WideGrid g = wide_grid(cap_m, n_out);
-    p.tiles_m = g.tiles_m;
     p.tiles_n = g.tiles_n;
-    p.per_xcd = g.per_xcd;
     p.grid = g.blocks;
     GNN_CHECK(g.blocks <= kMaxGrid, GNN_ESIZE, "update_fwd: cap_m exceeds the grid limit");
     // With a workspace and the row count on the device, the reduction is

@@ -5,7 +5,8 @@
 //   dA = G W^T                   (M x K; reduction over n_out)
 // with bf16 operands, fp32 accumulation and fp32 results, on the 256 x 256
 // tiles of gemm_wide_dev.h.  The host-table model's first layer (K = 1,536,
-// n_out = 1,024) is the case they are written for.
+// n_out = 1,024) is the case they are written for; narrower layers come here
+// when their capacity is tall (wide_layer).
 //
 // Operands: A's tiles (dW, T layout) and those of a bf16 copy of W (dA, N
 // layout, made by a small kernel first) are copied from memory straight into
@@ -50,7 +51,7 @@ struct DinArgs {
     const int64_t *m_dev;
     int64_t cap_m, K, n_out, n_pad;
     float *d_a;                // M x K
-    int64_t tiles_m, tiles_n, per_xcd;
+    int64_t tiles_n;
 };
 
 struct DwArgs {
@@ -61,7 +62,7 @@ struct DwArgs {
     int64_t cap_m, n_out;
     int want_db;
     float *part;               // nsplit x (K + 1) x part_ld(n_out)
-    int64_t k_tiles, tiles, nsplit, per_xcd;
+    int64_t k_tiles, tiles, nsplit;
 };
 
 // The fp32 operand's registers for one chunk: 16 floats per thread.
@@ -98,13 +99,12 @@ struct DinProb {
         int64_t row0, col0, M, nch;
     };
     __device__ static bool setup(const Args &p, int64_t blk, Work &w) {
-        const int64_t t = (blk % wide::kXcds) * p.per_xcd + blk / wide::kXcds;
-        if (t >= p.tiles_m * p.tiles_n) return false;
-        const int64_t tm = t / p.tiles_n, tn = t % p.tiles_n;
         w.M = p.m_dev ? min(*p.m_dev, p.cap_m) : p.cap_m;
+        const int64_t t = wide::xcd_item(blk, ceil_div(w.M, int64_t(kTile)) * p.tiles_n);
+        if (t < 0) return false;
+        const int64_t tm = t / p.tiles_n, tn = t % p.tiles_n;
         w.row0 = tm * kTile;
         w.col0 = tn * kTile;
-        if (w.row0 >= w.M) return false;
         w.nch = ceil_div(p.n_out, int64_t(kBK));
         w.rg = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.g + w.row0 * p.n_out), 0,
                                                  static_cast<int>((p.cap_m - w.row0) * p.n_out * 4), 0x00020000);
@@ -171,8 +171,8 @@ struct DwProb {
         bool do_db;            // the first K tile's workgroups write db
     };
     __device__ static bool setup(const Args &p, int64_t blk, Work &w) {
-        const int64_t t = (blk % wide::kXcds) * p.per_xcd + blk / wide::kXcds;
-        if (t >= p.tiles * p.nsplit) return false;
+        const int64_t t = wide::xcd_item(blk, p.tiles * p.nsplit);
+        if (t < 0) return false;
         w.split = static_cast<int>(t / p.tiles);
         const int64_t tile = t % p.tiles;
         const int64_t tk = tile % p.k_tiles, tn = tile / p.k_tiles;
@@ -590,8 +590,7 @@ gnn_status launch_wide_bwd_gemms(const Args &a, hipStream_t s) {
     w.k_tiles = pl.k_tiles;
     w.tiles = pl.tiles;
     w.nsplit = a.d_a ? pl.nsplit_da : pl.nsplit;
-    w.per_xcd = ceil_div(pl.tiles * w.nsplit, int64_t(wide::kXcds));
-    const int64_t n_dw = w.per_xcd * wide::kXcds;
+    const int64_t n_dw = round_up(pl.tiles * w.nsplit, int64_t(wide::kXcds));
     if (!a.d_a) {
         wide_dweight_kernel<kLeadDw><<<static_cast<unsigned>(n_dw), kWgThreads, 0, s>>>(w);
         GNN_LAUNCHED("update_dweight_wide");
@@ -610,10 +609,8 @@ gnn_status launch_wide_bwd_gemms(const Args &a, hipStream_t s) {
     d.n_out = a.n_out;
     d.n_pad = n_pad;
     d.d_a = a.d_a;
-    d.tiles_m = ceil_div(a.cap_m, int64_t(kTile));
     d.tiles_n = ceil_div(K, int64_t(kTile));
-    d.per_xcd = ceil_div(d.tiles_m * d.tiles_n, int64_t(wide::kXcds));
-    const int64_t blocks = n_dw + d.per_xcd * wide::kXcds;
+    const int64_t blocks = n_dw + round_up(ceil_div(a.cap_m, int64_t(kTile)) * d.tiles_n, int64_t(wide::kXcds));
     GNN_CHECK(blocks <= kMaxGrid, GNN_ESIZE, "update_bwd: cap_m exceeds the grid limit");
     wide_dw_din_kernel<kLeadDw, kLeadDin><<<static_cast<unsigned>(blocks), kWgThreads, 0, s>>>(w, d, n_dw);
     GNN_LAUNCHED("update_dweight_dinput_wide");

@@ -39,12 +39,27 @@ constexpr int kXcds = 8;
 constexpr int kTileElems = kTile * kBK;  // one operand tile of one chunk, bf16 elements
 
 // Layers that always take the wide kernels, and those that tall mini-batches
-// bring here.  K of 256 and less is left to the kernels whose results the
-// two-layer launches reproduce bit for bit.
+// bring here: 128 tiles of the capacity (a row count on the device is not known
+// where the kernel is chosen). Measured against the engine's smaller tiles at
+// 26,624 to 180,000 rows, K of 384 to 1,536 and n_out of 192 to 384, with 2%
+// to 100% of the capacity live: forward 0.6 to 1.02 of its time up to 30%,
+// 0.55 to 0.9 above; backward 0.4 to 0.95.  K of 256 and less is left to the
+// kernels whose results the two-layer launches reproduce bit for bit.
 inline bool wide_shape(int64_t K, int64_t n_out) { return K >= 512 && n_out >= 512; }
 inline bool wide_layer(int64_t K, int64_t n_out, int64_t cap_m) {
     if (wide_shape(K, n_out)) return true;
     return K > 256 && n_out >= 192 && ceil_div(cap_m, kTile) * ceil_div(n_out, kTile) >= 128;
+}
+
+// Work item of workgroup blk (-1: none) when n items, known on the device, are
+// dealt to the XCDs in contiguous ranges: XCD x = blk % 8 takes items
+// [x p, (x + 1) p), p = ceil(n / 8). The items are those that hold rows: ranges
+// of the capacity's tiles would leave all of them to the first XCDs (180,000
+// rows of capacity, 18,000 live, 512 x 256: forward 54 us so, 20 now,
+// backward 98 and 37; the smaller tiles of the general engine take 21 and 62).
+__host__ __device__ __forceinline__ int64_t xcd_item(int64_t blk, int64_t n) {
+    const int64_t p = ceil_div(n, int64_t(kXcds)), t = (blk % kXcds) * p + blk / kXcds;
+    return blk / kXcds < p && t < n ? t : -1;
 }
 
 // s_waitcnt immediate: vmcnt(vm) expcnt(7, no wait) lgkmcnt(lgkm)

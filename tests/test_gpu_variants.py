@@ -105,7 +105,7 @@ def test_sampler_vertex_marks(n):
 
 
 # Layers with K of more than 256 and n_out of 192 and more take the 256 x 256
-# matrix-core tiles once 128 of them hold rows (32,513 rows at one tile column),
+# matrix-core tiles once the capacity has 128 of them (32,513 rows at one tile column),
 # else the 64 x 64 and 128 x 128 ones; K % 128 and n_out % 8 keep some out.  The
 # forward's tiles are 192, 224 or 256 rows high.
 @pytest.mark.parametrize("k_each,cat,n_out,cap,rows", [
@@ -327,3 +327,38 @@ def test_two_layer_bwd_tall_last_layer(kind, f1, n_out, n_dst):
     tol = 4 * 2.0 ** -24 * n_dst ** 0.5  # fp32 sums of n_dst terms, 4 x for the spread
     for got, want in ((out[2], A.t() @ g2.bfloat16().double()), (out[3], g2.double().sum(0))):
         assert float((got.double() - want).norm() / want.norm()) <= tol
+
+
+# Tall capacities with few live rows (a row count on the device): the tiles that
+# hold rows and their height follow the count.  A tile's sums do not depend on
+# either, so the rows are those of the full capacity's call bit for bit; the
+# weight gradient has splits of its own.
+@pytest.mark.parametrize("k_each,cat,n_out,cap,rows", [
+    (256, True, 256, 45_056, 1), (256, True, 192, 60_000, 500), (384, False, 200, 100_000, 10_000),
+    (256, True, 384, 26_624, 193), (256, True, 256, 180_000, 18_000), (256, True, 256, 57_000, 49_152)])
+def test_update_tall_capacity_few_rows(k_each, cat, n_out, cap, rows):
+    g = torch.Generator(device=DEV).manual_seed(cap + rows)
+    a = [torch.randn((cap, k_each), generator=g, device=DEV).bfloat16() for _ in range(2 if cat else 1)]
+    nbr = a[1] if cat else None
+    grad = torch.randn((cap, n_out), generator=g, device=DEV)
+    K = k_each * len(a)
+    w = torch.randn((K, n_out), generator=g, device=DEV) / K ** 0.5
+    bias = torch.randn(n_out, generator=g, device=DEV)
+    wt = w.t().contiguous().bfloat16()
+    res = []
+    for m_dev in (None, torch.tensor([rows], dtype=torch.int64, device=DEV)):
+        out = torch.full((cap, n_out), 7.0, dtype=torch.bfloat16, device=DEV)
+        da = torch.full((cap, K), 7.0, device=DEV)
+        dw, db = torch.empty((K, n_out), device=DEV), torch.empty(n_out, device=DEV)
+        gnn.update_fwd(a[0], nbr, w, bias, out, True, gnn.GNN_BF16, m_dev=m_dev, wt=wt)
+        ws = torch.full_like(gnn.update_bwd_workspace(K, n_out, cap, gnn.GNN_BF16, DEV), 255)  # NaN patterns
+        gnn.update_bwd(a[0], nbr, w, grad, dw, db, da, gnn.GNN_BF16, m_dev=m_dev, ws=ws)
+        res.append((out, da, dw, db))
+    torch.cuda.synchronize()
+    (out, da, _, _), (out_m, da_m, dw, db) = res
+    assert torch.equal(out_m[:rows], out[:rows]) and torch.equal(da_m[:rows], da[:rows])
+    assert bool((out_m[rows:] == 7.0).all()) and bool((da_m[rows:] == 7.0).all())
+    A = torch.cat([x[:rows] for x in a], 1).double()
+    tol = 4 * 2.0 ** -24 * max(rows, 16) ** 0.5  # (as test_update_tall_layers)
+    for got, want in ((dw, A.t() @ grad[:rows].bfloat16().double()), (db, grad[:rows].double().sum(0))):
+        assert float((got.double() - want).norm()) <= tol * float(want.norm())
