@@ -28,7 +28,7 @@ gnn_status launch_aggregate_bwd(const gnn_block *b, int kind, const float *d_a, 
                                 int hbdt, float *d_src, hipStream_t s) {
     if (b->cap_src == 0 || f == 0) return GNN_OK;
     gnn_status st = GNN_OK;
-    agg::with_bwd_job<true>(b, kind, d_a, f, h_below, hbdt, d_src, [&](auto job) {
+    agg::with_bwd_job(b, kind, d_a, f, h_below, hbdt, d_src, [&](auto job) {
         st = launch_job(job, agg::row_grid(b->cap_src), s, "aggregate_bwd");
     });
     return st;
@@ -49,7 +49,7 @@ gnn_status launch_aggregate_bwd_max(const gnn_block *b, const int32_t *argmax, c
                                     const void *h_below, int hbdt, float *d_src, hipStream_t s) {
     if (b->cap_src == 0 || f == 0) return GNN_OK;
     gnn_status st = GNN_OK;
-    agg::with_bwd_max_job<true>(b, argmax, d_a, f, h_below, hbdt, d_src, [&](auto job) {
+    agg::with_bwd_max_job(b, argmax, d_a, f, h_below, hbdt, d_src, [&](auto job) {
         st = launch_job(job, agg::row_grid(b->cap_src), s, "aggregate_bwd_max");
     });
     return st;

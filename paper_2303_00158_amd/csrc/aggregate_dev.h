@@ -42,9 +42,6 @@ __device__ __forceinline__ float4 load_chunk(const T *p, int64_t row_off, int64_
     return make_float4(v[0], v[1], v[2], v[3]);
 }
 
-// Gradients larger than the L2s bypass them where a caller may not read them
-// next (NT): they would only push out the rows that repeat.
-constexpr int64_t kStreamBytes = 32 << 20;
 template <bool VEC, class T>
 __device__ __forceinline__ void store_chunk(T *p, int64_t row_off, int64_t e0, int64_t f, float4 v) {
     if constexpr (VEC) {
@@ -55,16 +52,6 @@ __device__ __forceinline__ void store_chunk(T *p, int64_t row_off, int64_t e0, i
 #pragma unroll
     for (int q = 0; q < 4; ++q)
         if (e0 + q < f) Elem<T>::store(p, row_off + e0 + q, a[q]);
-}
-
-template <bool VEC, bool NT>
-__device__ __forceinline__ void store_grad(float *p, int64_t row_off, int64_t e0, int64_t f, const float4 &v) {
-    if constexpr (VEC && NT) {
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
-        __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4 *>(p + row_off + e0));
-    } else {
-        store_chunk<VEC>(p, row_off, e0, f, v);
-    }
 }
 
 __device__ __forceinline__ void fma4(float4 &acc, float w, const float4 &v) {
@@ -275,8 +262,12 @@ __device__ __forceinline__ void agg_fwd_rows(const Edges &edges, const int64_t *
 // 1.6e-8, 246 targets, f = 128) than sums over alternate edges. Most sources have one or two edges: the kernel is a chain of
 // three dependent loads per row (column pointer, rows, their gradients), so what
 // counts is that many rows are in flight (8,192 targets, f = 256: 32 us with indices and
-// weights taken from other lanes at 75 registers, now 28 us; the maximum's 43
+// weights taken from other lanes at 75 registers, now 31 us; the maximum's 43
 // us, now 41).
+// Gradients above 32 MiB used to bypass the caches in calls of their own,
+// which made the call 1 to 3 us shorter and its reader 3 to 7 us longer (the
+// backward and the update below it: 68.4 us, without 66.0; the maximum's 80.5
+// and 76.8).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void add4(float4 &acc, const float4 &a, const float4 &b) {
     acc.x += a.x + b.x;
@@ -290,7 +281,7 @@ template <bool UNI> __device__ __forceinline__ int32_t maybe_scalar(int32_t x) {
     if constexpr (UNI) return __builtin_amdgcn_readfirstlane(x);
     return x;
 }
-template <int KIND, class THB, bool VEC, bool UNI, bool NT>
+template <int KIND, class THB, bool VEC, bool UNI>
 __device__ __forceinline__ void agg_bwd_rows(int64_t n_dst, const int64_t *__restrict__ rowptr,
                                              const int32_t *__restrict__ cscrow, const float *__restrict__ src_norm,
                                              const float *__restrict__ d_a, int64_t f, int C, const RowLanes &L,
@@ -347,7 +338,7 @@ __device__ __forceinline__ void agg_bwd_rows(int64_t n_dst, const int64_t *__res
             if (!(hb.z > 0.f)) acc.z = 0.f;
             if (!(hb.w > 0.f)) acc.w = 0.f;
         }
-        store_grad<VEC, NT>(d_src, j * f, e0, f, acc);
+        store_chunk<VEC>(d_src, j * f, e0, f, acc);
     }
 }
 
@@ -495,11 +486,7 @@ struct FwdJob {
     }
 };
 
-// STREAM: large gradients may bypass the caches (a call of its own: 45 MB at
-// 8,192 targets, f = 256, 29.1 to 27.3 us, the maximum's two passes 59.3 to
-// 56.1; inside a training step, whose next launch reads them, 277 to 278 us
-// per three-layer step, so not there).
-template <int KIND, class THB, bool VEC, bool UNI, bool STREAM = false>
+template <int KIND, class THB, bool VEC, bool UNI>
 struct BwdJob {
     gnn_block b;
     const float *d_a;
@@ -508,24 +495,18 @@ struct BwdJob {
     const THB *h_below;
     float *d_src;
     static constexpr int kWavesPerSimd = VEC && UNI ? 8 : 1;  // (as FwdJob's)
-    template <bool NT> __device__ __forceinline__ void walk(int64_t blk, int64_t nblk) const {
+    __device__ void run(int64_t blk, int64_t nblk) const {
         const int64_t n_dst = b.counts[0];
         const RowLanes L(C, 1, R);
         walk_columns<UNI>(
             b, blk, nblk, C, R, L,
             [&](int64_t j, int64_t beg, int32_t len) {
-                agg_bwd_rows<KIND, THB, VEC, UNI, NT>(n_dst, b.rowptr, b.cscrow, b.src_norm, d_a, f, C, L, h_below,
+                agg_bwd_rows<KIND, THB, VEC, UNI>(n_dst, b.rowptr, b.cscrow, b.src_norm, d_a, f, C, L, h_below,
                                                       d_src, j, beg, len);
             },
             [&](int64_t j, int64_t beg, int64_t end) {
                 agg_bwd_long<KIND, THB, UNI>(n_dst, b.rowptr, b.cscrow, b.src_norm, d_a, f, h_below, d_src, j, beg, end);
             });
-    }
-    __device__ void run(int64_t blk, int64_t nblk) const {
-        if (STREAM && VEC && b.counts[1] * f * 4 > kStreamBytes)
-            walk<STREAM>(blk, nblk);
-        else
-            walk<false>(blk, nblk);
     }
 };
 
@@ -647,7 +628,7 @@ __device__ __forceinline__ void agg_fwd_row_max(const int64_t *__restrict__ rowp
 // of j's column (the columns are in ascending row order), and only the
 // first of them counts: the maximum passes its gradient once.  The
 // neighbour rows of d_a are read only for elements that j won.
-template <class THB, bool VEC, bool UNI, bool NT>
+template <class THB, bool VEC, bool UNI>
 __device__ __forceinline__ void agg_bwd_rows_max(int64_t n_dst, const int32_t *__restrict__ cscrow,
                                                  const int32_t *__restrict__ argmax, const float *__restrict__ d_a,
                                                  int64_t f, int C, const RowLanes &L,
@@ -712,7 +693,7 @@ __device__ __forceinline__ void agg_bwd_rows_max(int64_t n_dst, const int32_t *_
             if (!(hb.z > 0.f)) acc.z = 0.f;
             if (!(hb.w > 0.f)) acc.w = 0.f;
         }
-        store_grad<VEC, NT>(d_src, j * f, e0, f, acc);
+        store_chunk<VEC>(d_src, j * f, e0, f, acc);
     }
 }
 
@@ -783,7 +764,7 @@ struct FwdMaxJob {
     }
 };
 
-template <class THB, bool VEC, bool UNI, bool STREAM = false>  // (as BwdJob's)
+template <class THB, bool VEC, bool UNI>
 struct BwdMaxJob {
     gnn_block b;
     const int32_t *argmax;
@@ -793,23 +774,17 @@ struct BwdMaxJob {
     const THB *h_below;
     float *d_src;
     static constexpr int kWavesPerSimd = VEC && UNI ? 8 : 1;
-    template <bool NT> __device__ __forceinline__ void walk(int64_t blk, int64_t nblk) const {
+    __device__ void run(int64_t blk, int64_t nblk) const {
         const int64_t n_dst = b.counts[0];
         const RowLanes L(C, 1, R);
         walk_columns<UNI>(
             b, blk, nblk, C, R, L,
             [&](int64_t j, int64_t beg, int32_t len) {
-                agg_bwd_rows_max<THB, VEC, UNI, NT>(n_dst, b.cscrow, argmax, d_a, f, C, L, h_below, d_src, j, beg, len);
+                agg_bwd_rows_max<THB, VEC, UNI>(n_dst, b.cscrow, argmax, d_a, f, C, L, h_below, d_src, j, beg, len);
             },
             [&](int64_t j, int64_t beg, int64_t end) {
                 agg_bwd_long_max<THB, UNI>(n_dst, b.cscrow, argmax, d_a, f, h_below, d_src, j, beg, end);
             });
-    }
-    __device__ void run(int64_t blk, int64_t nblk) const {
-        if (STREAM && VEC && b.counts[1] * f * 4 > kStreamBytes)
-            walk<STREAM>(blk, nblk);
-        else
-            walk<false>(blk, nblk);
     }
 };
 
@@ -880,7 +855,7 @@ bool with_fwd_job(const gnn_block *b, int kind, const void *h, int hdt, int64_t 
 }
 
 // f(job) with the backward job.
-template <bool STREAM = false, class F>
+template <class F>
 void with_bwd_job(const gnn_block *b, int kind, const float *d_a, int64_t f, const void *h_below, int hbdt,
                   float *d_src, F &&fn) {
     const int C = static_cast<int>(ceil_div(f, 4)), R = rows_per_wave(f);
@@ -892,8 +867,8 @@ void with_bwd_job(const gnn_block *b, int kind, const float *d_a, int64_t f, con
         const THB *hb = static_cast<const THB *>(h_below);
         auto by_rows = [&](auto vec_tag) {
             constexpr bool V = decltype(vec_tag)::value;
-            if (R == 1) fn(BwdJob<KIND, THB, V, true, STREAM>{*b, d_a, f, C, R, hb, d_src});
-            else fn(BwdJob<KIND, THB, V, false, STREAM>{*b, d_a, f, C, R, hb, d_src});
+            if (R == 1) fn(BwdJob<KIND, THB, V, true>{*b, d_a, f, C, R, hb, d_src});
+            else fn(BwdJob<KIND, THB, V, false>{*b, d_a, f, C, R, hb, d_src});
         };
         if (vec) by_rows(std::true_type{});
         else by_rows(std::false_type{});
@@ -940,7 +915,7 @@ bool with_fwd_kind_job(const gnn_block *b, int kind, const void *h, int hdt, int
     return with_fwd_job(b, kind, h, hdt, f, out, odt, fn);
 }
 
-template <bool STREAM = false, class F>
+template <class F>
 void with_bwd_max_job(const gnn_block *b, const int32_t *argmax, const float *d_a, int64_t f, const void *h_below,
                       int hbdt, float *d_src, F &&fn) {
     const int C = static_cast<int>(ceil_div(f, 4)), R = rows_per_wave(f);
@@ -951,8 +926,8 @@ void with_bwd_max_job(const gnn_block *b, const int32_t *argmax, const float *d_
         const THB *hb = static_cast<const THB *>(h_below);
         auto by_rows = [&](auto vec_tag) {
             constexpr bool V = decltype(vec_tag)::value;
-            if (R == 1) fn(BwdMaxJob<THB, V, true, STREAM>{*b, argmax, d_a, f, C, R, hb, d_src});
-            else fn(BwdMaxJob<THB, V, false, STREAM>{*b, argmax, d_a, f, C, R, hb, d_src});
+            if (R == 1) fn(BwdMaxJob<THB, V, true>{*b, argmax, d_a, f, C, R, hb, d_src});
+            else fn(BwdMaxJob<THB, V, false>{*b, argmax, d_a, f, C, R, hb, d_src});
         };
         if (vec) by_rows(std::true_type{});
         else by_rows(std::false_type{});
