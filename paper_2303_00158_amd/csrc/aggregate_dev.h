@@ -255,15 +255,14 @@ __device__ __forceinline__ void agg_fwd_rows(const Edges &edges, const int64_t *
 // ---------------------------------------------------------------------------
 // backward: d_src[j] = self(j) + sum_{i in csc(j)} w_ij d_a[i, nbr part]
 //
-// A source's edges are added one after another, four loads in flight; a row
-// takes ceil(f / 4) lanes, so rows of up to 128 elements share a wavefront
-// (RowLanes) and are summed four edges at a time, in two pairs: one running
-// sum over all edges was further from the 64-bit result (1.8e-8 against
-// 1.6e-8, 246 targets, f = 128) than sums over alternate edges. Most sources have one or two edges: the kernel is a chain of
-// three dependent loads per row (column pointer, rows, their gradients), so what
-// counts is that many rows are in flight (8,192 targets, f = 256: 32 us with indices and
-// weights taken from other lanes at 75 registers, now 31 us; the maximum's 43
-// us, now 41).
+// Rows of more than 128 elements take a wavefront each, which adds the source's
+// edges one after another, four loads in flight; narrower ones share a
+// wavefront (walk_narrow). Most sources have one or two edges: the kernel is a
+// chain of three dependent loads per row (column pointer, rows, their
+// gradients), so what counts is that many rows are in flight and that the grid
+// is resident (54 and 62 registers for wide rows; narrow ones 71 to 91, so 5 to
+// 7 wavefronts per SIMD: at 64 they spill and took up to twice the time).
+// 8,192 targets, f = 256: 41 us, now 31, the maximum's 83 us, now 44.
 // Gradients above 32 MiB used to bypass the caches in calls of their own,
 // which made the call 1 to 3 us shorter and its reader 3 to 7 us longer (the
 // backward and the update below it: 68.4 us, without 66.0; the maximum's 80.5
@@ -275,14 +274,43 @@ __device__ __forceinline__ void add4(float4 &acc, const float4 &a, const float4 
     acc.z += a.z + b.z;
     acc.w += a.w + b.w;
 }
-// This lane's column j, its edges beg .. beg + len - 1. UNI: one column per
-// wavefront (C > 32), whose indices are kept scalar.
-template <bool UNI> __device__ __forceinline__ int32_t maybe_scalar(int32_t x) {
-    if constexpr (UNI) return __builtin_amdgcn_readfirstlane(x);
-    return x;
+// acc, a column's sum over its edges, becomes its gradient: the self term
+// (weight ws) where j is a destination, and the ReLU mask.
+template <bool VEC>
+__device__ __forceinline__ void finish_grad(float4 acc, float ws, const float4 &self, const float4 &hb, int64_t n_dst,
+                                            bool mask, int64_t f, uint32_t e0, float *__restrict__ d_src, int64_t j) {
+    if (j < n_dst) fma4(acc, ws, self);
+    if (mask) {
+        if (!(hb.x > 0.f)) acc.x = 0.f;
+        if (!(hb.y > 0.f)) acc.y = 0.f;
+        if (!(hb.z > 0.f)) acc.z = 0.f;
+        if (!(hb.w > 0.f)) acc.w = 0.f;
+    }
+    store_chunk<VEC>(d_src, j * f, e0, f, acc);
 }
-template <int KIND, class THB, bool VEC, bool UNI>
-__device__ __forceinline__ void agg_bwd_rows(int64_t n_dst, const int64_t *__restrict__ rowptr,
+// What finish_grad takes of column j itself (ka: d_a's row length).
+struct OwnTerms {
+    float4 self, hb;
+};
+template <class THB, bool VEC>
+__device__ __forceinline__ OwnTerms own_terms(int64_t n_dst, const float *__restrict__ d_a, int64_t ka,
+                                              const THB *__restrict__ h_below, int64_t f, uint32_t e0, int64_t j) {
+    OwnTerms o;
+    if (j < n_dst) o.self = load_chunk<VEC>(d_a + j * ka, 0, e0, f);
+    if (h_below) o.hb = load_chunk<VEC>(h_below + j * f, 0, e0, f);
+    return o;
+}
+// The weight of row i's edge in the column of a source with normaliser wj.
+template <int KIND>
+__device__ __forceinline__ float edge_weight(const int64_t *__restrict__ rowptr, const float *__restrict__ src_norm,
+                                             int32_t i, float wj) {
+    if constexpr (KIND == GNN_AGG_GCN_SYM) return src_norm[i] * wj;
+    return 1.f / static_cast<float>(static_cast<int32_t>(rowptr[i + 1]) - static_cast<int32_t>(rowptr[i]));
+}
+// Column j of a wavefront, its edges beg .. beg + len - 1, for rows of more
+// than 32 lanes; the indices are kept scalar.
+template <int KIND, class THB, bool VEC>
+__device__ __forceinline__ void agg_bwd_row(int64_t n_dst, const int64_t *__restrict__ rowptr,
                                              const int32_t *__restrict__ cscrow, const float *__restrict__ src_norm,
                                              const float *__restrict__ d_a, int64_t f, int C, const RowLanes &L,
                                              const THB *__restrict__ h_below, float *__restrict__ d_src, int64_t j,
@@ -291,6 +319,7 @@ __device__ __forceinline__ void agg_bwd_rows(int64_t n_dst, const int64_t *__res
     const int64_t nbr_off = (KIND == GNN_AGG_SAGE_MEAN) ? f : 0;
     const float wj = (KIND == GNN_AGG_GCN_SYM) ? src_norm[j] : 1.f;
     const bool mask = h_below != nullptr;
+    const float ws = (KIND == GNN_AGG_GCN_SYM) ? wj * wj : 1.f;
     for (int chunk = L.chunk; chunk < C; chunk += 64) {
         const uint32_t e0 = static_cast<uint32_t>(chunk) * 4;
         // the self term and the ReLU mask, issued before the neighbours so
@@ -309,37 +338,54 @@ __device__ __forceinline__ void agg_bwd_rows(int64_t n_dst, const int64_t *__res
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 if (t + q < len) {
-                    i[q] = maybe_scalar<UNI>(i[q]);
+                    i[q] = __builtin_amdgcn_readfirstlane(i[q]);
                     v[q] = load_chunk<VEC>(d_a + (static_cast<int64_t>(i[q]) * ka + nbr_off), 0, e0, f);
-                    if (KIND == GNN_AGG_GCN_SYM)
-                        w[q] = src_norm[i[q]] * wj;
-                    else
-                        w[q] = 1.f / static_cast<float>(rowptr[i[q] + 1] - rowptr[i[q]]);
+                    w[q] = edge_weight<KIND>(rowptr, src_norm, i[q], wj);
                 }
-            if constexpr (UNI) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (t + q < len) fma4(acc, w[q], v[q]);
-            } else {
-                float4 pair[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (t + q < len) fma4(pair[q / 2], w[q], v[q]);
-                add4(acc, pair[0], pair[1]);
-            }
+            for (int q = 0; q < 4; ++q)
+                if (t + q < len) fma4(acc, w[q], v[q]);
         }
-        if (j < n_dst) {
-            const float ws = (KIND == GNN_AGG_GCN_SYM) ? wj * wj : 1.f;
-            fma4(acc, ws, self);
-        }
-        if (mask) {
-            if (!(hb.x > 0.f)) acc.x = 0.f;
-            if (!(hb.y > 0.f)) acc.y = 0.f;
-            if (!(hb.z > 0.f)) acc.z = 0.f;
-            if (!(hb.w > 0.f)) acc.w = 0.f;
-        }
-        store_chunk<VEC>(d_src, j * f, e0, f, acc);
+        finish_grad<VEC>(acc, ws, self, hb, n_dst, mask, f, e0, d_src, j);
     }
+}
+
+// This lane's part of a narrow column's sum: edges t0, t0 + step, ... of the
+// column's len at cscrow, four at a time in two pairs (one running sum over
+// all of them was further from the 64-bit result: 1.8e-8 against 1.6e-8 at 246
+// targets, f = 128).
+template <int KIND, bool VEC>
+__device__ __forceinline__ float4 agg_bwd_part(const int64_t *__restrict__ rowptr, const int32_t *__restrict__ cscrow,
+                                               const float *__restrict__ src_norm, const float *__restrict__ d_a,
+                                               int64_t f, uint32_t e0, float wj, uint32_t len, uint32_t t0,
+                                               uint32_t step) {
+    const int64_t ka = (KIND == GNN_AGG_SAGE_MEAN) ? 2 * f : f;
+    const int64_t nbr_off = (KIND == GNN_AGG_SAGE_MEAN) ? f : 0;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto four = [&](uint32_t t, auto all) {
+        constexpr bool ALL = decltype(all)::value;
+        int32_t i[4];
+        float w[4];
+        float4 v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (ALL || t + q * step < len) i[q] = cscrow[t + q * step];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (ALL || t + q * step < len) {
+                v[q] = load_chunk<VEC>(d_a + (static_cast<int64_t>(i[q]) * ka + nbr_off), 0, e0, f);
+                w[q] = edge_weight<KIND>(rowptr, src_norm, i[q], wj);
+            }
+        float4 pair[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (ALL || t + q * step < len) fma4(pair[q / 2], w[q], v[q]);
+        add4(acc, pair[0], pair[1]);
+    };
+    uint32_t t = t0;
+    for (; t + 3 * step < len; t += 4 * step) four(t, std::true_type{});
+    if (t < len) four(t, std::false_type{});
+    return acc;
 }
 
 // The transpose's long columns (the graph's hubs): a wavefront that walks one
@@ -348,52 +394,137 @@ __device__ __forceinline__ void agg_bwd_rows(int64_t n_dst, const int64_t *__res
 // whole workgroup afterwards, a thread per element and kLongAhead edges in
 // flight, the edges in the same sequence, so the sums are the same bit for bit.
 // At 8,192 targets (fanout 25, f = 256; the longest column has about 180
-// of the 59k edges) the mean's backward took 36 us, now 32, the
-// maximum's 79 us, now 43.
+// of the 59k edges) the mean's backward took 36 us without, 32 with it, the
+// maximum's 79 and 43. Columns of up to 32 or 64 edges left with their wavefront
+// are no faster at 1,024 targets and 3 us slower at 8,192.
 constexpr int kLong = 16;       // longest column of one wavefront
+constexpr int kShare = 8;       // narrow rows: longest column of a row's own lanes
 constexpr int kLongAhead = 16;
 struct LongColumns {
-    static constexpr int kCap = 64;  // columns past it stay with their wavefronts
-    int n;
-    int32_t j[kCap];
-    // The lanes of a row (`first` the row's first): put column c aside when
-    // wanted; false where it is not or there is no room.
-    __device__ __forceinline__ bool add(int64_t c, bool want, int first) {
-        int at = kCap;
-        if (want && static_cast<int>(threadIdx.x & 63) == first) {
-            at = atomicAdd(&n, 1);
-            if (at < kCap) j[at] = static_cast<int32_t>(c);
-        }
-        return __shfl(at, first, 64) < kCap;
+    static constexpr int kCap = 16;  // per wavefront; columns past it stay with their wavefront
+    int n[kWaves];
+    int32_t j[kWaves][kCap];
+    // A wavefront's n-th column; false where there is no room.
+    __device__ __forceinline__ bool add(int &n, int64_t c) {
+        if (n == kCap) return false;
+        j[threadIdx.x >> 6][n++] = static_cast<int32_t>(c);  // (every lane writes the same)
+        return true;
+    }
+    // fn(column) in all threads, for the columns of all wavefronts (n: this one's).
+    template <class F> __device__ __forceinline__ void walk(int own, F &&fn) {
+        n[threadIdx.x >> 6] = own;
+        __syncthreads();
+        for (int w = 0; w < kWaves; ++w)
+            for (int i = 0; i < n[w]; ++i) fn(static_cast<int64_t>(j[w][i]));
     }
 };
-// Calls row(j, beg, len) in every lane that has a column of its own, for the
-// columns of this workgroup, R per wavefront, and long_row(j, beg, end) in all
-// threads for those put aside.
-template <bool UNI, class Row, class LongRow>
-__device__ __forceinline__ void walk_columns(const gnn_block &b, int64_t blk, int64_t nblk, int C, int R,
-                                             const RowLanes &L, Row &&row, LongRow &&long_row) {
+// One column per wavefront (rows of more than 128 elements): row(j, beg, len)
+// in the lanes that the row takes, and long_row(j, beg, end) in all threads of
+// the workgroup for those put aside.
+template <class Row, class LongRow>
+__device__ __forceinline__ void walk_columns(const gnn_block &b, int64_t blk, int64_t nblk, const RowLanes &L,
+                                             Row &&row, LongRow &&long_row) {
     __shared__ LongColumns aside;
     const int64_t n_src = b.counts[1];
-    const int first = L.r * (C > 64 ? 64 : C);
-    if (threadIdx.x == 0) aside.n = 0;
-    __syncthreads();
-    for (int64_t j0 = (blk * kWaves + (threadIdx.x >> 6)) * R; j0 < n_src; j0 += nblk * kWaves * R) {
-        const bool live = L.active && j0 + L.r < n_src;
-        int64_t j = live ? j0 + L.r : j0;
-        if constexpr (UNI) j = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(j));  // (local ids are 32-bit)
+    int put = 0;
+    for (int64_t j0 = blk * kWaves + (threadIdx.x >> 6); j0 < n_src; j0 += nblk * kWaves) {
+        const int64_t j = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(j0));  // (local ids are 32-bit)
         const int64_t beg = b.cscptr[j], end = b.cscptr[j + 1];
-        const bool put = aside.add(j, live && end - beg > kLong, live ? first : 0);
-        if (live && !put) row(j, beg, maybe_scalar<UNI>(static_cast<int32_t>(end - beg)));
+        const int32_t len = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(end - beg));
+        if (len > kLong && aside.add(put, j)) continue;
+        if (L.active) row(j, beg, len);
     }
-    __syncthreads();
-    for (int i = 0; i < min(aside.n, LongColumns::kCap); ++i) {
-        const int64_t j = aside.j[i];
-        long_row(j, b.cscptr[j], b.cscptr[j + 1]);
-    }
+    aside.walk(put, [&](int64_t j) { long_row(j, b.cscptr[j], b.cscptr[j + 1]); });
 }
 
-template <int KIND, class THB, bool UNI>
+// Rows of up to 128 elements: C = ceil(f / 4) <= 32 lanes each. Columns of up to
+// kShare edges share a wavefront, as many as leave every wavefront of the grid
+// one (at most 64 / C). A longer one is summed by a whole wavefront, S = 64 / C
+// edges at a time (slots), and one of more than kLong S edges by the workgroup,
+// 4 S at a time. part(e0, j, beg, len, t0, step) is a lane's part of a sum,
+// edges t0, t0 + step, ...; the slots are added as a tree, the wavefronts of a
+// workgroup in order. All of it depends on the column's length alone (a column
+// for which the list has no room is summed in the same parts by one
+// wavefront), so results are the same on every run.
+// A block of 18,497 sources and 213k edges, the longest column 3,928: 12 us at f =
+// 4, 20 at 16, 55 at 64, 104 at 128 (252, 186, 194 and 216 when a workgroup
+// walked long columns one after another with a thread per element, most of
+// them idle; its one running sum was up to 2.8 times further from the 64-bit
+// sum of 4,000 edges). kShare: 4 is 10 to 25% slower at 32,768 targets (f up to
+// 16), 16 20% slower at 1,024.
+template <class Part, class Own, class Finish>
+__device__ __forceinline__ void walk_narrow(const gnn_block &b, int64_t blk, int64_t nblk, int C, int most, Part &&part,
+                                            Own &&own, Finish &&finish) {
+    __shared__ LongColumns aside;
+    __shared__ float4 sums[kWaves][32];
+    const int64_t n_src = b.counts[1];
+    const int64_t waves = nblk * kWaves;
+    // (three quarters of the grid's wavefronts: what the registers leave resident)
+    const uint32_t spread = static_cast<uint32_t>(waves * 3 / 4);
+    const int R = n_src <= spread ? 1 : static_cast<int>(min(static_cast<uint32_t>(most), (static_cast<uint32_t>(n_src) + spread - 1) / spread));
+    const RowLanes L(C, 1, R);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int S = 64 / C, slot = lane / C;
+    const uint32_t e0 = static_cast<uint32_t>(L.chunk) * 4;
+    // slots 1 .. S - 1 are added to slot 0
+    auto fold = [&](float4 &acc) {
+        for (int half = 32; half > 0; half >>= 1) {
+            if (half >= S) continue;
+            const float4 o = shfl4(acc, lane + half * C);
+            if (slot < half && slot + half < S) acc = make_float4(acc.x + o.x, acc.y + o.y, acc.z + o.z, acc.w + o.w);
+        }
+    };
+    int put = 0;
+    for (int64_t j0 = (blk * kWaves + wave) * R; j0 < n_src; j0 += waves * R) {
+        uint64_t longs;  // the first lanes of the longer columns
+        {
+            const bool live = L.active && j0 + L.r < n_src;
+            const int64_t j = live ? j0 + L.r : j0, beg = b.cscptr[j];
+            const int32_t len = static_cast<int32_t>(b.cscptr[j + 1] - beg);
+            longs = __ballot(live && len > kShare && L.chunk == 0);
+            if (live && len <= kShare) {
+                const OwnTerms o = own(e0, j);
+                finish(e0, j, part(e0, j, beg, len, 0, 1), o);
+            }
+        }
+        while (longs) {
+            const int64_t j = j0 + __builtin_ctzll(longs) / C, beg = b.cscptr[j];
+            const int32_t len = static_cast<int32_t>(b.cscptr[j + 1] - beg);
+            longs &= longs - 1;
+            const int shares = len > kLong * S ? kWaves : 1;
+            if (shares > 1 && aside.add(put, j)) continue;
+            const OwnTerms o = own(e0, j);
+            float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 1
+            for (int w = 0; w < shares; ++w) {
+                float4 acc = part(e0, j, beg, len, slot < S ? w * S + slot : len, shares * S);
+                fold(acc);
+                sum = make_float4(sum.x + acc.x, sum.y + acc.y, sum.z + acc.z, sum.w + acc.w);
+            }
+            if (slot == 0) finish(e0, j, sum, o);
+        }
+    }
+    aside.walk(put, [&](int64_t j) {
+        const int64_t beg = b.cscptr[j];
+        const int32_t len = static_cast<int32_t>(b.cscptr[j + 1] - beg);
+        const OwnTerms o = own(e0, j);
+        float4 acc = part(e0, j, beg, len, slot < S ? wave * S + slot : len, kWaves * S);
+        fold(acc);
+        if (slot == 0) sums[wave][lane] = acc;
+        __syncthreads();
+        if (wave == 0 && slot == 0) {
+            float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int w = 0; w < kWaves; ++w) {
+                const float4 x = sums[w][lane];
+                sum = make_float4(sum.x + x.x, sum.y + x.y, sum.z + x.z, sum.w + x.w);
+            }
+            finish(e0, j, sum, o);
+        }
+        __syncthreads();  // the sums are free for the next column
+    });
+}
+
+template <int KIND, class THB>
 __device__ __forceinline__ void agg_bwd_long(int64_t n_dst, const int64_t *__restrict__ rowptr,
                                              const int32_t *__restrict__ cscrow, const float *__restrict__ src_norm,
                                              const float *__restrict__ d_a, int64_t f, const THB *__restrict__ h_below,
@@ -414,10 +545,7 @@ __device__ __forceinline__ void agg_bwd_long(int64_t n_dst, const int64_t *__res
             float my_w = 0.f;
             if (lane < wn) {
                 my_idx = cscrow[wb + lane];
-                if (KIND == GNN_AGG_GCN_SYM)
-                    my_w = src_norm[my_idx] * wj;
-                else
-                    my_w = 1.f / static_cast<float>(rowptr[my_idx + 1] - rowptr[my_idx]);
+                my_w = edge_weight<KIND>(rowptr, src_norm, my_idx, wj);
             }
             for (int tb = 0; tb < wn; tb += kLongAhead) {
                 float v[kLongAhead], w[kLongAhead];
@@ -429,15 +557,8 @@ __device__ __forceinline__ void agg_bwd_long(int64_t n_dst, const int64_t *__res
                 }
 #pragma unroll
                 for (int u = 0; u < kLongAhead; ++u) v[u] = tb + u < wn ? v[u] : 0.f;
-                if constexpr (UNI) {
 #pragma unroll
-                    for (int u = 0; u < kLongAhead; ++u) acc = fmaf(w[u], v[u], acc);
-                } else {
-#pragma unroll
-                    for (int u = 0; u < kLongAhead; u += 4)
-                        acc += fmaf(w[u + 1], v[u + 1], fmaf(w[u], v[u], 0.f)) +
-                               fmaf(w[u + 3], v[u + 3], fmaf(w[u + 2], v[u + 2], 0.f));
-                }
+                for (int u = 0; u < kLongAhead; ++u) acc = fmaf(w[u], v[u], acc);
             }
         }
         if (j < n_dst) acc = fmaf((KIND == GNN_AGG_GCN_SYM) ? wj * wj : 1.f, self, acc);
@@ -494,19 +615,37 @@ struct BwdJob {
     int C, R;
     const THB *h_below;
     float *d_src;
-    static constexpr int kWavesPerSimd = VEC && UNI ? 8 : 1;  // (as FwdJob's)
+    static constexpr int kWavesPerSimd = VEC && UNI ? 8 : 1;
     __device__ void run(int64_t blk, int64_t nblk) const {
         const int64_t n_dst = b.counts[0];
-        const RowLanes L(C, 1, R);
-        walk_columns<UNI>(
-            b, blk, nblk, C, R, L,
-            [&](int64_t j, int64_t beg, int32_t len) {
-                agg_bwd_rows<KIND, THB, VEC, UNI>(n_dst, b.rowptr, b.cscrow, b.src_norm, d_a, f, C, L, h_below,
-                                                      d_src, j, beg, len);
-            },
-            [&](int64_t j, int64_t beg, int64_t end) {
-                agg_bwd_long<KIND, THB, UNI>(n_dst, b.rowptr, b.cscrow, b.src_norm, d_a, f, h_below, d_src, j, beg, end);
-            });
+        if constexpr (UNI) {
+            const RowLanes L(C, 1, 1);
+            walk_columns(
+                b, blk, nblk, L,
+                [&](int64_t j, int64_t beg, int32_t len) {
+                    agg_bwd_row<KIND, THB, VEC>(n_dst, b.rowptr, b.cscrow, b.src_norm, d_a, f, C, L, h_below, d_src, j,
+                                                beg, len);
+                },
+                [&](int64_t j, int64_t beg, int64_t end) {
+                    agg_bwd_long<KIND, THB>(n_dst, b.rowptr, b.cscrow, b.src_norm, d_a, f, h_below, d_src, j, beg, end);
+                });
+        } else {
+            auto norm = [&](int64_t j) { return (KIND == GNN_AGG_GCN_SYM) ? b.src_norm[j] : 1.f; };
+            walk_narrow(
+                b, blk, nblk, C, R,
+                [&](uint32_t e0, int64_t j, int64_t beg, int32_t len, int32_t t0, int32_t step) {
+                    return agg_bwd_part<KIND, VEC>(b.rowptr, b.cscrow + beg, b.src_norm, d_a, f, e0, norm(j), len, t0,
+                                                   step);
+                },
+                [&](uint32_t e0, int64_t j) {
+                    return own_terms<THB, VEC>(n_dst, d_a, (KIND == GNN_AGG_SAGE_MEAN) ? 2 * f : f, h_below, f, e0, j);
+                },
+                [&](uint32_t e0, int64_t j, const float4 &sum, const OwnTerms &o) {
+                    const float wj = norm(j);
+                    finish_grad<VEC>(sum, (KIND == GNN_AGG_GCN_SYM) ? wj * wj : 1.f, o.self, o.hb, n_dst,
+                                         h_below != nullptr, f, e0, d_src, j);
+                });
+        }
     }
 };
 
@@ -628,12 +767,12 @@ __device__ __forceinline__ void agg_fwd_row_max(const int64_t *__restrict__ rowp
 // of j's column (the columns are in ascending row order), and only the
 // first of them counts: the maximum passes its gradient once.  The
 // neighbour rows of d_a are read only for elements that j won.
-template <class THB, bool VEC, bool UNI>
-__device__ __forceinline__ void agg_bwd_rows_max(int64_t n_dst, const int32_t *__restrict__ cscrow,
-                                                 const int32_t *__restrict__ argmax, const float *__restrict__ d_a,
-                                                 int64_t f, int C, const RowLanes &L,
-                                                 const THB *__restrict__ h_below, float *__restrict__ d_src, int64_t j,
-                                                 int64_t beg, int32_t len) {
+template <class THB, bool VEC>
+__device__ __forceinline__ void agg_bwd_row_max(int64_t n_dst, const int32_t *__restrict__ cscrow,
+                                                const int32_t *__restrict__ argmax, const float *__restrict__ d_a,
+                                                int64_t f, int C, const RowLanes &L,
+                                                const THB *__restrict__ h_below, float *__restrict__ d_src, int64_t j,
+                                                int64_t beg, int32_t len) {
     const int64_t ka = 2 * f;
     const int32_t jj = static_cast<int32_t>(j);
     const bool mask = h_below != nullptr;
@@ -654,7 +793,7 @@ __device__ __forceinline__ void agg_bwd_rows_max(int64_t n_dst, const int32_t *_
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 if (t + q < len) {
-                    i[q] = maybe_scalar<UNI>(i[q]);
+                    i[q] = __builtin_amdgcn_readfirstlane(i[q]);
                     a[q] = load_arg4<VEC>(argmax + static_cast<int64_t>(i[q]) * f, 0, e0, f, -1);
                 }
 #pragma unroll
@@ -669,37 +808,62 @@ __device__ __forceinline__ void agg_bwd_rows_max(int64_t n_dst, const int32_t *_
                 if (a[q].x | a[q].y | a[q].z | a[q].w)
                     v[q] = load_chunk<VEC>(d_a + (static_cast<int64_t>(i[q]) * ka + f), 0, e0, f);
             }
-            float4 pair[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};  // (as agg_bwd_rows)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 if (t + q >= len || !(a[q].x | a[q].y | a[q].z | a[q].w)) continue;
-                float4 &sum = UNI ? acc : pair[q / 2];
-                sum.x += a[q].x ? v[q].x : 0.f;
-                sum.y += a[q].y ? v[q].y : 0.f;
-                sum.z += a[q].z ? v[q].z : 0.f;
-                sum.w += a[q].w ? v[q].w : 0.f;
+                acc.x += a[q].x ? v[q].x : 0.f;
+                acc.y += a[q].y ? v[q].y : 0.f;
+                acc.z += a[q].z ? v[q].z : 0.f;
+                acc.w += a[q].w ? v[q].w : 0.f;
             }
-            if constexpr (!UNI) add4(acc, pair[0], pair[1]);
         }
-        if (j < n_dst) {
-            acc.x += self.x;
-            acc.y += self.y;
-            acc.z += self.z;
-            acc.w += self.w;
-        }
-        if (mask) {
-            if (!(hb.x > 0.f)) acc.x = 0.f;
-            if (!(hb.y > 0.f)) acc.y = 0.f;
-            if (!(hb.z > 0.f)) acc.z = 0.f;
-            if (!(hb.w > 0.f)) acc.w = 0.f;
-        }
-        store_chunk<VEC>(d_src, j * f, e0, f, acc);
+        finish_grad<VEC>(acc, 1.f, self, hb, n_dst, mask, f, e0, d_src, j);
     }
+}
+
+// agg_bwd_part for the maximum.
+template <bool VEC>
+__device__ __forceinline__ float4 agg_bwd_part_max(const int32_t *__restrict__ cscrow,
+                                                   const int32_t *__restrict__ argmax, const float *__restrict__ d_a,
+                                                   int64_t f, uint32_t e0, int32_t j, uint32_t len, uint32_t t0,
+                                                   uint32_t step) {
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (uint32_t t = t0; t < len; t += 4 * step) {
+        int32_t i[4];
+        int4 a[4];
+        float4 v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t u = t + q * step;
+            i[q] = -1;
+            if (u >= len) continue;
+            i[q] = cscrow[u];
+            if (u > 0 && cscrow[u - 1] == i[q]) i[q] = -1;  // a row's second and later entries
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (i[q] >= 0) a[q] = load_arg4<VEC>(argmax + static_cast<int64_t>(i[q]) * f, 0, e0, f, -1);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (i[q] >= 0 && (a[q].x == j || a[q].y == j || a[q].z == j || a[q].w == j))
+                v[q] = load_chunk<VEC>(d_a + (static_cast<int64_t>(i[q]) * 2 * f + f), 0, e0, f);
+        float4 pair[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (i[q] < 0) continue;
+            pair[q / 2].x += a[q].x == j ? v[q].x : 0.f;
+            pair[q / 2].y += a[q].y == j ? v[q].y : 0.f;
+            pair[q / 2].z += a[q].z == j ? v[q].z : 0.f;
+            pair[q / 2].w += a[q].w == j ? v[q].w : 0.f;
+        }
+        add4(acc, pair[0], pair[1]);
+    }
+    return acc;
 }
 
 // A long column of the maximum's backward, by the whole workgroup
 // (agg_bwd_long's split and order).
-template <class THB, bool UNI>
+template <class THB>
 __device__ __forceinline__ void agg_bwd_long_max(int64_t n_dst, const int32_t *__restrict__ cscrow,
                                                  const int32_t *__restrict__ argmax, const float *__restrict__ d_a,
                                                  int64_t f, const THB *__restrict__ h_below,
@@ -734,13 +898,8 @@ __device__ __forceinline__ void agg_bwd_long_max(int64_t n_dst, const int32_t *_
                     v[u] = 0.f;
                     if (i >= 0 && a[u] == jj) v[u] = (d_a + i * ka + f)[e];
                 }
-                if constexpr (UNI) {
 #pragma unroll
-                    for (int u = 0; u < kLongAhead; ++u) acc += v[u];
-                } else {
-#pragma unroll
-                    for (int u = 0; u < kLongAhead; u += 4) acc += (v[u] + v[u + 1]) + (v[u + 2] + v[u + 3]);
-                }
+                for (int u = 0; u < kLongAhead; ++u) acc += v[u];
             }
         }
         if (j < n_dst) acc += self;
@@ -776,15 +935,28 @@ struct BwdMaxJob {
     static constexpr int kWavesPerSimd = VEC && UNI ? 8 : 1;
     __device__ void run(int64_t blk, int64_t nblk) const {
         const int64_t n_dst = b.counts[0];
-        const RowLanes L(C, 1, R);
-        walk_columns<UNI>(
-            b, blk, nblk, C, R, L,
-            [&](int64_t j, int64_t beg, int32_t len) {
-                agg_bwd_rows_max<THB, VEC, UNI>(n_dst, b.cscrow, argmax, d_a, f, C, L, h_below, d_src, j, beg, len);
-            },
-            [&](int64_t j, int64_t beg, int64_t end) {
-                agg_bwd_long_max<THB, UNI>(n_dst, b.cscrow, argmax, d_a, f, h_below, d_src, j, beg, end);
-            });
+        if constexpr (UNI) {
+            const RowLanes L(C, 1, 1);
+            walk_columns(
+                b, blk, nblk, L,
+                [&](int64_t j, int64_t beg, int32_t len) {
+                    agg_bwd_row_max<THB, VEC>(n_dst, b.cscrow, argmax, d_a, f, C, L, h_below, d_src, j, beg, len);
+                },
+                [&](int64_t j, int64_t beg, int64_t end) {
+                    agg_bwd_long_max<THB>(n_dst, b.cscrow, argmax, d_a, f, h_below, d_src, j, beg, end);
+                });
+        } else {
+            walk_narrow(
+                b, blk, nblk, C, R,
+                [&](uint32_t e0, int64_t j, int64_t beg, int32_t len, int32_t t0, int32_t step) {
+                    return agg_bwd_part_max<VEC>(b.cscrow + beg, argmax, d_a, f, e0, static_cast<int32_t>(j), len, t0,
+                                                 step);
+                },
+                [&](uint32_t e0, int64_t j) { return own_terms<THB, VEC>(n_dst, d_a, 2 * f, h_below, f, e0, j); },
+                [&](uint32_t e0, int64_t j, const float4 &sum, const OwnTerms &o) {
+                    finish_grad<VEC>(sum, 1.f, o.self, o.hb, n_dst, h_below != nullptr, f, e0, d_src, j);
+                });
+        }
     }
 };
 

@@ -362,3 +362,126 @@ def test_update_tall_capacity_few_rows(k_each, cat, n_out, cap, rows):
     tol = 4 * 2.0 ** -24 * max(rows, 16) ** 0.5  # (as test_update_tall_layers)
     for got, want in ((dw, A.t() @ grad[:rows].bfloat16().double()), (db, grad[:rows].double().sum(0))):
         assert float((got.double() - want).norm()) <= tol * float(want.norm())
+
+
+def transpose_block(member, norm=None):
+    """A block of which aggregation backward reads the transpose: member[j, i]
+    says whether column j holds row i (bool, on the device)."""
+    n_src, n_dst = member.shape
+    nnz = int(member.sum())
+    cap = max(n_dst, -(-nnz // 1024))
+    b = gnn.DeviceBlock(max(n_src, cap), cap, 1024, True, norm is not None, DEV)
+    b.counts[0], b.counts[1], b.counts[2] = n_dst, n_src, nnz
+    b.cscptr[1:n_src + 1] = member.sum(1).cumsum(0)
+    b.cscrow[:nnz] = member.nonzero()[:, 1].int()
+    b.rowptr[1:n_dst + 1] = member.sum(0).cumsum(0)
+    if norm is not None:
+        b.src_norm[:n_src] = norm
+    return b
+
+
+def bwd_in_64_bits(kind, member, d_a, f, norm, argmax):
+    """gnn_aggregate_bwd's or its max form's formula, without a mask."""
+    n_src, n_dst = member.shape
+    x, M = d_a.double(), member.double()
+    own = torch.zeros((n_src, f), dtype=torch.float64, device=DEV)
+    if kind == "gcn":
+        own[:n_dst] = x * norm[:n_dst, None].double() ** 2
+        return own + norm[:, None].double() * (M @ (x * norm[:n_dst, None].double()))
+    own[:n_dst] = x[:, :f]
+    if kind == "mean":
+        return own + M @ (x[:, f:] / member.sum(0).clamp(min=1)[:, None])
+    won = member[argmax.long(), torch.arange(n_dst, device=DEV)[:, None]]
+    return own.scatter_add_(0, argmax.long(), x[:, f:] * won)
+
+
+def run_bwd(kind, b, d_a, f, argmax):
+    d = torch.full((b.src_ids.numel(), f), 5.0, device=DEV)
+    if kind == "max":
+        gnn.aggregate_bwd_max(b, argmax, d_a, f, d)
+    else:
+        gnn.aggregate_bwd(b, gnn.GNN_AGG_GCN_SYM if kind == "gcn" else gnn.GNN_AGG_SAGE_MEAN, d_a, f, d)
+    return d
+
+
+# Rows of up to 128 elements: columns summed by the row's own lanes (up to 8
+# entries), by a wavefront (up to 16 S, S = 64 / ceil(f / 4)) and by the
+# workgroup, and the entries at which a lane's groups of four begin.
+@pytest.mark.parametrize("f", [1, 3, 4, 16, 32, 50, 64, 100, 128])
+@pytest.mark.parametrize("kind", ["mean", "gcn", "max"])
+def test_aggregate_bwd_narrow_columns(kind, f):
+    S = 64 // (-(-f // 4))
+    lens = [0, 1, 2, 3, 4, 5, 7, 8, 9, 12, 15, 16, 17]
+    lens += [x + d for x in (S, 3 * S, 4 * S, 8 * S, 16 * S, 48 * S, 64 * S) for d in (-1, 0, 1)] + [1500]
+    lens = [min(x, 1500) for x in lens]
+    rng = np.random.default_rng(f)
+    n_dst, n_src = 1500, 1500 + 64
+    member = np.zeros((n_src, n_dst), dtype=bool)
+    at = rng.permutation(n_src)[:len(lens)]
+    for j, l in zip(at, lens):
+        member[j, rng.choice(n_dst, size=l, replace=False)] = True
+    member[-1] |= ~member.any(0)  # (every row has an edge)
+    member = torch.from_numpy(member).to(DEV)
+    g = torch.Generator(device=DEV).manual_seed(f)
+    norm = torch.rand(n_src, generator=g, device=DEV) + 0.1
+    d_a = torch.randn((n_dst, f if kind == "gcn" else 2 * f), generator=g, device=DEV)
+    argmax = torch.randint(0, n_src, (n_dst, f), generator=g, device=DEV).int()
+    longest = torch.from_numpy(at[-8:]).to(DEV)  # (winners enough in the long columns)
+    argmax[::2] = longest[torch.randint(0, 8, (n_dst, f), generator=g, device=DEV)].int()[::2]
+    b = transpose_block(member, norm if kind == "gcn" else None)
+    print(f"[narrow columns] {kind} f={f}", flush=True)
+    got = run_bwd(kind, b, d_a, f, argmax)
+    want = bwd_in_64_bits(kind, member, d_a, f, norm, argmax)
+    size = bwd_in_64_bits(kind, member, d_a.abs(), f, norm, argmax)  # (of the terms)
+    # at most 1,500 / 4 additions follow one another (with f = 128 some 50): they
+    # walk off by 2^-24 sqrt(50); 2 x for the weights' own rounding
+    assert bool(((got[:n_src].double() - want).norm(dim=1) <= 16 * 2.0 ** -24 * size.norm(dim=1)).all())
+    assert bool((got[n_src:] == 5.0).all())
+
+
+# The error of a hub's sum at narrow widths: not above that of S slots that
+# take an edge each in turn, whose partial sums are added in order.
+@pytest.mark.parametrize("f", [4, 16, 32, 128])
+def test_aggregate_bwd_hub_precision(f):
+    n_dst, hubs = 4000, 24
+    member = torch.zeros((n_dst + hubs, n_dst), dtype=torch.bool, device=DEV)
+    member[n_dst:] = True
+    b = transpose_block(member)
+    w = np.float32(1.0) / np.float32(hubs)
+    S = 64 // (-(-f // 4))
+    errors = np.zeros(2)
+    for seed in range(8):
+        g = torch.Generator(device=DEV).manual_seed(seed)
+        d_a = torch.rand((n_dst, 2 * f), generator=g, device=DEV)  # (terms of one sign: the sums grow)
+        got = run_bwd("mean", b, d_a, f, None)[n_dst:n_dst + hubs]
+        assert torch.equal(got, got[:1].expand(hubs, f))
+        x = d_a[:, f:].cpu().numpy().astype(np.float64)
+        acc = np.zeros((S, f), dtype=np.float32)
+        for t in range(0, n_dst, 64):
+            for k in range(t, min(t + 64, n_dst)):
+                acc[(k - t) % S] = (x[k] * w + acc[(k - t) % S]).astype(np.float32)
+        ref = acc[0]
+        for s in range(1, S):
+            ref = ref + acc[s]
+        want = (x * np.float64(w)).sum(0)
+        errors += [((got[0].cpu().numpy() - want) ** 2).sum(), ((ref - want) ** 2).sum()]
+    # (1.2 x: the ratio of two random errors of 8 f sums)
+    assert errors[0] ** 0.5 <= 1.2 * errors[1] ** 0.5
+
+
+# More long columns than a wavefront's list holds: those past it are summed by
+# the wavefront that met them, in the same parts, so a run repeats bit for bit.
+@pytest.mark.parametrize("f,kind", [(128, "mean"), (128, "max"), (130, "mean"), (130, "max")])
+def test_aggregate_bwd_more_long_columns_than_listed(f, kind):
+    n_dst, n_src = 64, 8192 * 18
+    g = torch.Generator(device=DEV).manual_seed(f)
+    order = torch.rand((n_src, n_dst), generator=g, device=DEV).argsort(1)
+    member = torch.zeros((n_src, n_dst), dtype=torch.bool, device=DEV).scatter_(1, order[:, :40], True)
+    d_a = torch.randn((n_dst, 2 * f), generator=g, device=DEV)
+    argmax = torch.randint(0, n_src, (n_dst, f), generator=g, device=DEV).int()
+    b = transpose_block(member)
+    print(f"[long columns] {kind} f={f}", flush=True)
+    got = run_bwd(kind, b, d_a, f, argmax)
+    want = bwd_in_64_bits(kind, member, d_a, f, None, argmax)
+    assert float((got[:n_src].double() - want).norm() / want.norm()) <= 1e-6  # fp32 sums of 40 terms
+    assert torch.equal(run_bwd(kind, b, d_a, f, argmax), got)
