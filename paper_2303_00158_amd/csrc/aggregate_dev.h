@@ -308,7 +308,9 @@ __device__ __forceinline__ float edge_weight(const int64_t *__restrict__ rowptr,
     return 1.f / static_cast<float>(static_cast<int32_t>(rowptr[i + 1]) - static_cast<int32_t>(rowptr[i]));
 }
 // Column j of a wavefront, its edges beg .. beg + len - 1, for rows of more
-// than 32 lanes; the indices are kept scalar.
+// than 32 lanes: the lanes load the indices and weights of 32 edges at a time
+// (with a load per edge and lane the backward of 1,024 targets, f = 256, took 8.5
+// us, now 7.0).
 template <int KIND, class THB, bool VEC>
 __device__ __forceinline__ void agg_bwd_row(int64_t n_dst, const int64_t *__restrict__ rowptr,
                                              const int32_t *__restrict__ cscrow, const float *__restrict__ src_norm,
@@ -320,33 +322,39 @@ __device__ __forceinline__ void agg_bwd_row(int64_t n_dst, const int64_t *__rest
     const float wj = (KIND == GNN_AGG_GCN_SYM) ? src_norm[j] : 1.f;
     const bool mask = h_below != nullptr;
     const float ws = (KIND == GNN_AGG_GCN_SYM) ? wj * wj : 1.f;
-    for (int chunk = L.chunk; chunk < C; chunk += 64) {
-        const uint32_t e0 = static_cast<uint32_t>(chunk) * 4;
-        // the self term and the ReLU mask, issued before the neighbours so
-        // that their latency overlaps the sum
+    const int lane = threadIdx.x & 63;
+    // (every lane that entered stays in the loop: its edges are read by the others)
+    for (int c0 = 0; c0 < C; c0 += 64) {
+        const bool active = c0 + L.chunk < C;
+        const uint32_t e0 = active ? static_cast<uint32_t>(c0 + L.chunk) * 4 : 0;
         float4 self, hb;
         if (j < n_dst) self = load_chunk<VEC>(d_a + j * ka, 0, e0, f);
         if (mask) hb = load_chunk<VEC>(h_below + j * f, 0, e0, f);
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int32_t t = 0; t < len; t += 4) {
-            int32_t i[4];
-            float w[4];
+        for (int32_t wb = 0; wb < len; wb += 32) {  // (a row has more than 32 lanes)
+            const int32_t wn = min(32, len - wb);
+            const int32_t my_idx = lane < wn ? cscrow[beg + wb + lane] : 0;
             float4 v[4];
+            auto load = [&](int32_t t) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (t + q < len) i[q] = cscrow[beg + t + q];
+                for (int q = 0; q < 4; ++q)
+                    if (t + q < wn) {
+                        const int64_t i = __builtin_amdgcn_readlane(my_idx, t + q);
+                        v[q] = load_chunk<VEC>(d_a + (i * ka + nbr_off), 0, e0, f);
+                    }
+            };
+            load(0);
+            // (the weights behind the first rows: they wait for loads of their own)
+            const float my_w = lane < wn ? edge_weight<KIND>(rowptr, src_norm, my_idx, wj) : 0.f;
+            for (int32_t t = 0; t < wn; t += 4) {
+                if (t > 0) load(t);
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (t + q < len) {
-                    i[q] = __builtin_amdgcn_readfirstlane(i[q]);
-                    v[q] = load_chunk<VEC>(d_a + (static_cast<int64_t>(i[q]) * ka + nbr_off), 0, e0, f);
-                    w[q] = edge_weight<KIND>(rowptr, src_norm, i[q], wj);
-                }
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (t + q < len) fma4(acc, w[q], v[q]);
+                for (int q = 0; q < 4; ++q)
+                    if (t + q < wn)
+                        fma4(acc, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), t + q)), v[q]);
+            }
         }
-        finish_grad<VEC>(acc, ws, self, hb, n_dst, mask, f, e0, d_src, j);
+        if (active) finish_grad<VEC>(acc, ws, self, hb, n_dst, mask, f, e0, d_src, j);
     }
 }
 

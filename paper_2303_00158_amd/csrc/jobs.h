@@ -9,6 +9,8 @@
 // bounds of 256 threads, and the LDS of both is reserved.
 #pragma once
 
+#include <algorithm>
+
 #include "internal.h"
 
 namespace gnn {
@@ -25,9 +27,12 @@ __global__ void __launch_bounds__(256, job_waves<J>(0)) job_kernel(J j) {
 
 // Workgroups [0, na) run a, [na_pad, grid) run b; na_pad (a multiple of 8)
 // keeps b's logical workgroup index congruent to its physical one modulo the
-// XCD count, which jobs that map work to XCDs rely on.
+// XCD count, which jobs that map work to XCDs rely on. The stricter of the two
+// jobs' register bounds holds for both (the wide aggregation backward beside
+// dW's reduction: 86 registers without, and 44 us for its two launches of a
+// three-layer step instead of 38).
 template <class A, class B>
-__global__ void __launch_bounds__(256) job2_kernel(A a, unsigned na, unsigned na_pad, B b) {
+__global__ void __launch_bounds__(256, std::max(job_waves<A>(0), job_waves<B>(0))) job2_kernel(A a, unsigned na, unsigned na_pad, B b) {
     if (blockIdx.x < na_pad) {
         if (blockIdx.x < na) a.run(blockIdx.x, na);
     } else {
