@@ -212,22 +212,51 @@ __device__ __forceinline__ void agg_fwd_rows(const Edges &edges, const int64_t *
         for (int e = 0; e < E; ++e) acc[e] = 0.f;
         for (int32_t wb = 0; wb < mine; wb += 64) {
             const int wn = min(64, mine - wb);
-            for (int t = L.slot; t < wn; t += 4 * S) {
-                int32_t j[4];
-                float w[4];
-                RowElems<T, E, VEC, Edges::kRound> v[4];
+            if constexpr (Edges::kRound) {
+                for (int t = L.slot; t < wn; t += 4 * S) {
+                    int32_t j[4];
+                    float w[4];
+                    RowElems<T, E, VEC, true> v[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (t + q * S < wn) j[q] = edges.at(row, beg, wb + t + q * S);
+                    for (int q = 0; q < 4; ++q)
+                        if (t + q * S < wn) j[q] = edges.at(row, beg, wb + t + q * S);
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (t + q * S < wn) {
-                        w[q] = (KIND == GNN_AGG_GCN_SYM) ? wi * edges.norm[j[q]] : 1.f;
-                        v[q].load(edges.x, static_cast<int64_t>(j[q]) * edges.stride, e0, f);
-                    }
+                    for (int q = 0; q < 4; ++q)
+                        if (t + q * S < wn) {
+                            w[q] = (KIND == GNN_AGG_GCN_SYM) ? wi * edges.norm[j[q]] : 1.f;
+                            v[q].load(edges.x, static_cast<int64_t>(j[q]) * edges.stride, e0, f);
+                        }
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (t + q * S < wn) v[q].add(acc, w[q]);
+                    for (int q = 0; q < 4; ++q)
+                        if (t + q * S < wn) v[q].add(acc, w[q]);
+                }
+            } else {
+                // Four edges that are all there (ALL) need no guard around each
+                // load; the guards cost a small call more than its loads
+                // (1,024 targets, f = 256, GCN: 8.1 us, now 6.2). The table's
+                // launch above lost by it (23 us to 28 beside the sort of a
+                // three-layer step).
+                auto four = [&](int t, auto all) {
+                    constexpr bool ALL = decltype(all)::value;
+                    int32_t j[4];
+                    float w[4];
+                    RowElems<T, E, VEC, false> v[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (ALL || t + q * S < wn) j[q] = edges.at(row, beg, wb + t + q * S);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (ALL || t + q * S < wn) {
+                            w[q] = (KIND == GNN_AGG_GCN_SYM) ? wi * edges.norm[j[q]] : 1.f;
+                            v[q].load(edges.x, static_cast<int64_t>(j[q]) * edges.stride, e0, f);
+                        }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (ALL || t + q * S < wn) v[q].add(acc, w[q]);
+                };
+                int t = L.slot;
+                for (; t + 3 * S < wn; t += 4 * S) four(t, std::true_type{});
+                if (t < wn) four(t, std::false_type{});
             }
         }
         // fold the slots into slot 0
