@@ -485,3 +485,21 @@ def test_aggregate_bwd_more_long_columns_than_listed(f, kind):
     want = bwd_in_64_bits(kind, member, d_a, f, None, argmax)
     assert float((got[:n_src].double() - want).norm() / want.norm()) <= 1e-6  # fp32 sums of 40 terms
     assert torch.equal(run_bwd(kind, b, d_a, f, argmax), got)
+
+
+# The bf16 conversion of the kernels against the integer rule, by the gather's
+# vector and element-wise forms: every sign and exponent with mantissas at and
+# beside the ties (to even and to odd), carries into the exponent, subnormals,
+# infinities, and quiet and signalling NaNs.
+@pytest.mark.parametrize("dim", [8, 5])
+def test_bf16_conversion_bits(dim):
+    mantissas = np.array([0, 1, 2, 0x7fff, 0x8000, 0x8001, 0xffff, 0x10000, 0x17fff, 0x18000, 0x18001, 0x3f8000,
+                          0x3fffff, 0x400000, 0x408000, 0x7f7fff, 0x7f8000, 0x7f8001, 0x7fffff], dtype=np.uint32)
+    head = np.arange(512, dtype=np.uint32) << 23  # sign and exponent
+    bits = (head[:, None] | mantissas).reshape(-1)
+    bits = np.concatenate([bits, np.zeros(-bits.size % 40, dtype=np.uint32)]).reshape(-1, dim)
+    table = torch.from_numpy(bits.view(np.float32)).to(DEV)
+    out = torch.empty(bits.shape, dtype=torch.bfloat16, device=DEV)
+    gnn.gather_features(table, torch.arange(bits.shape[0], device=DEV), out)
+    got = out.view(torch.int16).cpu().numpy().view(np.uint16)
+    assert np.array_equal(got, oracle.f32_to_bf16_bits(bits.view(np.float32)).reshape(bits.shape))
