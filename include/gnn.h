@@ -382,8 +382,8 @@ gnn_status gnn_two_layer_fwd_max(const gnn_block *last, int32_t fanout, const vo
  * h_below = h1) followed by gnn_update_bwd on each layer with the same caps
  * (cap_m1 for layer 1, last->cap_dst for layer 2); where gnn_update_bwd takes
  * its wide kernels for a tall layer 2, dw2 and db2 are the same sums in
- * another order.  Needs f1 % 4 == 0 and f1 > 128, K1 <= 256, f0 % 4 == 0, 8-byte aligned bf16 rows and h1;
- * else GNN_EUNSUPPORTED.
+ * another order.  Needs f1 % 4 == 0 and f1 > 128, K1 <= 256, f0 % 4 == 0,
+ * 8-byte aligned bf16 rows and h1; else GNN_EUNSUPPORTED.
  * ------------------------------------------------------------------------ */
 gnn_status gnn_two_layer_bwd_workspace_size(gnn_agg kind, int64_t f0, int64_t f1, int64_t n_out, int64_t cap_m1,
                                             int64_t cap_m2, size_t *bytes);
@@ -448,7 +448,10 @@ gnn_status gnn_update_fwd(const void *a_self, const void *a_nbr, gnn_dtype adt, 
  *   results are bitwise reproducible.  Layers with K and n_out both >= 512
  *   split the rows over more workgroups, so their workspace is larger (up
  *   to 64 partial copies of dW; in bf16 also a bf16 copy of W that dA
- *   reads).  ws [device] must be 256-byte aligned
+ *   reads).  So do bf16 layers with K > 256 and n_out >= 192 once cap_m
+ *   has 128 tiles of 256 rows by 256 columns (their workspace stays within
+ *   the allocation-free entry's scratch): for those, cap_m decides the
+ *   kernel and with it the order of the sums.  ws [device] must be 256-byte aligned
  *   and hold gnn_update_bwd_workspace_size bytes; no state is kept in it
  *   between calls; calls sharing it must not overlap. */
 gnn_status gnn_update_bwd_workspace_size(int64_t k, int64_t n_out, int64_t cap_m, gnn_dtype gemm_dt, size_t *bytes);
