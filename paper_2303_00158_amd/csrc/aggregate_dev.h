@@ -474,10 +474,10 @@ __device__ __forceinline__ void walk_columns(const gnn_block &b, int64_t blk, in
     aside.walk(put, [&](int64_t j) { long_row(j, b.cscptr[j], b.cscptr[j + 1]); });
 }
 
-// Rows of up to 128 elements: C = ceil(f / 4) <= 32 lanes each. Columns of up to
-// kShare edges share a wavefront, as many as leave every wavefront of the grid
-// one (at most 64 / C). A longer one is summed by a whole wavefront, S = 64 / C
-// edges at a time (slots), and one of more than kLong S edges by the workgroup,
+// Rows of up to 128 elements: C = ceil(f / 4) <= 32 lanes each, S = 64 / C of them
+// in a wavefront. Columns of up to kShare edges share a wavefront, as many as
+// leave every wavefront of the grid one (at most S). A longer one is summed by a
+// whole wavefront, S edges at a time (slots), and one of more than kLong S edges by the workgroup,
 // 4 S at a time. part(e0, j, beg, len, t0, step) is a lane's part of a sum,
 // edges t0, t0 + step, ...; the slots are added as a tree, the wavefronts of a
 // workgroup in order. All of it depends on the column's length alone (a column
@@ -490,7 +490,7 @@ __device__ __forceinline__ void walk_columns(const gnn_block &b, int64_t blk, in
 // sum of 4,000 edges). kShare: 4 is 10 to 25% slower at 32,768 targets (f up to
 // 16), 16 20% slower at 1,024.
 template <class Part, class Own, class Finish>
-__device__ __forceinline__ void walk_narrow(const gnn_block &b, int64_t blk, int64_t nblk, int C, int most, Part &&part,
+__device__ __forceinline__ void walk_narrow(const gnn_block &b, int64_t blk, int64_t nblk, int C, int S, Part &&part,
                                             Own &&own, Finish &&finish) {
     __shared__ LongColumns aside;
     __shared__ float4 sums[kWaves][32];
@@ -498,11 +498,12 @@ __device__ __forceinline__ void walk_narrow(const gnn_block &b, int64_t blk, int
     const int64_t waves = nblk * kWaves;
     // (three quarters of the grid's wavefronts: what the registers leave resident)
     const uint32_t spread = static_cast<uint32_t>(waves * 3 / 4);
-    const int R = n_src <= spread ? 1 : static_cast<int>(min(static_cast<uint32_t>(most), (static_cast<uint32_t>(n_src) + spread - 1) / spread));
-    const RowLanes L(C, 1, R);
+    const int R = n_src <= spread ? 1
+                                  : static_cast<int>(min(static_cast<uint32_t>(S),
+                                                         (static_cast<uint32_t>(n_src) + spread - 1) / spread));
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int S = 64 / C, slot = lane / C;
-    const uint32_t e0 = static_cast<uint32_t>(L.chunk) * 4;
+    const int slot = lane / C, chunk = lane - slot * C;
+    const uint32_t e0 = static_cast<uint32_t>(chunk) * 4;
     // slots 1 .. S - 1 are added to slot 0
     auto fold = [&](float4 &acc) {
         for (int half = 32; half > 0; half >>= 1) {
@@ -515,10 +516,10 @@ __device__ __forceinline__ void walk_narrow(const gnn_block &b, int64_t blk, int
     for (int64_t j0 = (blk * kWaves + wave) * R; j0 < n_src; j0 += waves * R) {
         uint64_t longs;  // the first lanes of the longer columns
         {
-            const bool live = L.active && j0 + L.r < n_src;
-            const int64_t j = live ? j0 + L.r : j0, beg = b.cscptr[j];
+            const bool live = slot < R && j0 + slot < n_src;
+            const int64_t j = live ? j0 + slot : j0, beg = b.cscptr[j];
             const int32_t len = static_cast<int32_t>(b.cscptr[j + 1] - beg);
-            longs = __ballot(live && len > kShare && L.chunk == 0);
+            longs = __ballot(live && len > kShare && chunk == 0);
             if (live && len <= kShare) {
                 const OwnTerms o = own(e0, j);
                 finish(e0, j, part(e0, j, beg, len, 0, 1), o);
